@@ -49,7 +49,8 @@ def stored_bytes_per_lup(model: str, schedule: int) -> float:
 
 
 # the step kernels and the strip table that shapes their traffic
-KERNEL_SOURCES = ("lb_internal.h", "lb_kernels.h", "lb_strip.h", "lb_strip_table.h", "lb_wide.h", "lb_wide2.h", "lb_wmom.h")
+KERNEL_SOURCES = ("lb_internal.h", "lb_kernels.h", "lb_strip.h", "lb_strip_table.h", "lb_wide.h", "lb_wide2.h", "lb_wmom.h",
+                  "lb_block.h", "lb_block_table.h")
 
 
 def code_of(text: str) -> str:
@@ -351,7 +352,8 @@ def main():
     bpl = BYTES_PER_LUP[model]
     sbpl = stored_bytes_per_lup(model, cfg.schedule)
     achieved = bpl * fluid / (us_kernel * 1e-6) / 1e9 if us_kernel > 0 else None
-    kname = ({3: "lb_strip_", 4: "lb_wide_", 5: "lb_wide2_", 6: "lb_wmom_"}[cfg.schedule] + ("bin" if model == "binary" else "vdw")
+    kname = ({3: "lb_strip_", 4: "lb_wide_" if model == "binary" else "lb_block_", 5: "lb_wide2_", 6: "lb_block_"}[cfg.schedule]
+             + ("bin" if model == "binary" else "vdw")
              if cfg.schedule in (3, 4, 5, 6) else f"lb_step_kernel_{model}_{cfg.tile_rows}")
     traffic = traffic_from_profiles(kname, args.workload, cfg.asdict())
     config.update({"model": model, "fluid_nodes": fluid, "launch": cfg.asdict(), "bytes_per_lup": bpl,

@@ -29,6 +29,7 @@
 #include "lb_wide.h"
 #include "lb_wide2.h"
 #include "lb_wmom.h"
+#include "lb_block.h"
 #include "lb_thermo.h"
 
 using namespace lbk;
@@ -327,6 +328,11 @@ struct lb_ctx {
     StripDev* d_strips = nullptr;
     int nstrips = 0;
     int xcd_start[9] = {};    // strip runs of the 8 XCDs
+    BlockDev* d_blocks = nullptr;   // tiles of the block kernels (an allocation of its own)
+    size_t blocks_cap = 0;
+    int nblocks = 0;
+    int block_k = 0;          // steps per launch of the block kernels; 0: other schedules
+    int block_shape = 0;
     float* d_lnow = nullptr;
     float* d_hist = nullptr;
     long long* d_hist_t = nullptr;
@@ -395,10 +401,93 @@ lb_status set_storage(lb_ctx* c, int m) {
 // output columns per strip of the row-sweep schedules (3: one wavefront, 4: a workgroup)
 int strip_width(const lb_launch_config& cfg) { return cfg.schedule >= 4 ? WIDE_OUT : STRIP_OUT; }
 
-// time steps one launch of the step kernel advances (schedule 5: two per sweep)
-int steps_per_launch(const lb_launch_config& cfg) { return cfg.schedule == 5 ? 2 : 1; }
+// time steps one launch of the step kernel advances
+int steps_per_launch(const lb_ctx* c) { return c->block_k > 0 ? c->block_k : (c->cfg.schedule == 5 ? 2 : 1); }
+
+// Schedules 4 (van der Waals) and 6 advance several steps per launch in tiles
+// (lb_block.h); the others sweep rows or single-step tiles.
+bool uses_blocks(const lb_ctx* c) { return c->cfg.schedule == (c->model == LB_VDW ? 4 : 6); }
+
+lb_status upload_blocks(lb_ctx* c) {
+    const bool vdw = c->model == LB_VDW;
+    const BlockPlan p = plan_block_tiles(c->G, c->active, vdw);
+    if (p.tiles > 0x7ffffff0u) return fail(LB_EINVAL, "tile table too large");
+    if (p.tiles == 0) return LB_OK;   // every capillary is retired
+    std::vector<BlockDev> t;
+    build_blocks(c->G, c->active, p.K, block_rx(p.shape), block_ry(p.shape, vdw), block_align(p.shape, vdw), &t);
+    if (t.size() > c->blocks_cap) {
+        HIP_TRY(hipStreamSynchronize(c->stream));
+        (void)hipFree(c->d_blocks);
+        c->d_blocks = nullptr;
+        c->blocks_cap = 0;
+        if (hipMalloc(&c->d_blocks, sizeof(BlockDev) * t.size()) != hipSuccess)
+            return fail(LB_ENOMEM, "device allocation of the tile table failed");
+        c->blocks_cap = t.size();
+    }
+    HIP_TRY(hipMemcpyAsync(c->d_blocks, t.data(), sizeof(BlockDev) * t.size(), hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    c->nblocks = (int)t.size();
+    c->block_k = p.K;
+    c->block_shape = p.shape;
+    return LB_OK;
+}
+
+template <typename S, int MODEL, typename CT>
+void launch_block_f(lb_ctx* c, const BlockArgs& a, int grid) {
+    const dim3 g(grid), b(S::NT);
+    if constexpr (MODEL == 0) {
+        if (c->any_force)
+            hipLaunchKernelGGL((lb_block_vdw<S, CT, true>), g, b, 0, c->stream, a);
+        else
+            hipLaunchKernelGGL((lb_block_vdw<S, CT, false>), g, b, 0, c->stream, a);
+    } else {
+        // the collision's non-shear part in CT (the shear relaxation is exact enough in FP32)
+        if (c->any_force)
+            hipLaunchKernelGGL((lb_block_bin<S, CT, float, true>), g, b, 0, c->stream, a);
+        else
+            hipLaunchKernelGGL((lb_block_bin<S, CT, float, false>), g, b, 0, c->stream, a);
+    }
+}
+
+template <int MODEL, typename CT>
+void launch_block_s(lb_ctx* c, const BlockArgs& a, int grid) {
+    if (c->block_shape == 0)
+        launch_block_f<BlockShape<32, 32, 32>, MODEL, CT>(c, a, grid);
+    else if constexpr (MODEL == 0)
+        launch_block_f<BlockShape<64, 32, 16>, MODEL, CT>(c, a, grid);
+    else
+        launch_block_f<BlockShape<64, 24, 12>, MODEL, CT>(c, a, grid);
+}
+
+// One launch of `steps` steps (at most block_k) of the block kernels.
+void enqueue_block(lb_ctx* c, int steps) {
+    if (c->nblocks == 0) return;
+    BlockArgs a;
+    a.caps = c->d_caps;
+    a.blocks = c->d_blocks;
+    a.nblocks = c->nblocks;
+    a.arena0 = c->arena[0];
+    a.arena1 = c->arena[1];
+    a.cur = c->cur;
+    a.halo = 2 * c->block_k;
+    a.steps = steps;
+    const int grid = 8 * ((c->nblocks + 7) / 8);
+    if (c->model == LB_VDW) {
+        if (c->cfg.fp64_arith)
+            launch_block_s<0, double>(c, a, grid);
+        else
+            launch_block_s<0, float>(c, a, grid);
+    } else {
+        if (c->cfg.fp64_arith)
+            launch_block_s<1, double>(c, a, grid);
+        else
+            launch_block_s<1, float>(c, a, grid);
+    }
+}
 
 lb_status upload_tiles(lb_ctx* c) {
+    drop_graphs(c);
+    c->nstrips = c->nblocks = c->block_k = 0;
     std::vector<TileDev> tiles;
     build_tiles(c->G, c->active, c->cfg.tile_rows, tiles);
     if ((int)tiles.size() > c->L.max_tiles) return fail(LB_EINVAL, "tile table overflow");
@@ -407,15 +496,15 @@ lb_status upload_tiles(lb_ctx* c) {
         HIP_TRY(hipMemcpyAsync(c->d_tiles, tiles.data(), sizeof(TileDev) * tiles.size(), hipMemcpyHostToDevice,
                                c->stream));
     std::vector<StripDev> strips;
-    build_strips(c->G, c->active, c->cfg.chunk_rows, strip_width(c->cfg), 2, &strips, nullptr, c->xcd_start);
+    if (!uses_blocks(c))
+        build_strips(c->G, c->active, c->cfg.chunk_rows, strip_width(c->cfg), 2, &strips, nullptr, c->xcd_start);
     if ((int)strips.size() > c->L.max_strips) return fail(LB_EINVAL, "strip table overflow");
     c->nstrips = (int)strips.size();
     if (!strips.empty())
         HIP_TRY(hipMemcpyAsync(c->d_strips, strips.data(), sizeof(StripDev) * strips.size(), hipMemcpyHostToDevice,
                                c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
-    drop_graphs(c);
-    return LB_OK;
+    return uses_blocks(c) ? upload_blocks(c) : LB_OK;
 }
 
 template <int MODEL, int TY, bool INIT, typename R>
@@ -466,8 +555,6 @@ void launch_strip_f(lb_ctx* c, const StripArgs& a, int grid, bool fused) {
     } else {
         if (fused)
             hipLaunchKernelGGL((lb_wide2_bin<MT, CT, ST, FORCE>), dim3(grid), dim3(WIDE_THREADS), 0, c->stream, a);
-        else if (c->cfg.schedule == 6)
-            hipLaunchKernelGGL((lb_wmom_bin<MT, CT, ST, FORCE>), dim3(grid), dim3(WIDE_THREADS), 0, c->stream, a);
         else if (wide)
             hipLaunchKernelGGL((lb_wide_bin<MT, CT, ST, FORCE>), dim3(grid), dim3(WIDE_THREADS), 0, c->stream, a);
         else
@@ -544,17 +631,28 @@ void enqueue_step(lb_ctx* c, bool init, bool fused = false) {
     }
 }
 
+// Enqueue one launch of `steps` steps (at most steps_per_launch).
+void enqueue_launch(lb_ctx* c, int steps) {
+    if (uses_blocks(c))
+        enqueue_block(c, steps);
+    else
+        enqueue_step(c, false, steps == 2);
+}
+
+// Launches in a captured graph: graph_steps steps, in whole launches.
+int graph_launches(const lb_ctx* c) { return c->cfg.graph_steps / steps_per_launch(c); }
+
 // Every launch reads arena cur and writes the other one, so each flips cur,
-// whether it advances one time step or two.  A run of graph_steps steps is
+// however many time steps it advances.  A run of graph_launches launches is
 // one graph per starting arena (capture does not execute).
 lb_status capture_graph(lb_ctx* c, int p) {
-    const int spl = steps_per_launch(c->cfg);
-    const int launches = c->cfg.graph_steps / spl;
+    const int spl = steps_per_launch(c);
+    const int launches = graph_launches(c);
     const int keep = c->cur;
     c->cur = p;
     HIP_TRY(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
     for (int s = 0; s < launches; ++s) {
-        enqueue_step(c, false, spl == 2);
+        enqueue_launch(c, spl);
         c->cur ^= 1;
     }
     c->cur = keep;
@@ -567,15 +665,15 @@ lb_status capture_graph(lb_ctx* c, int p) {
 
 bool graphs_used(const lb_ctx* c, long n) {
     const int K = c->cfg.graph_steps;
-    return K >= 2 && (K % 2) == 0 && n >= K && c->ntiles > 0;
+    return K >= 2 && (K % 2) == 0 && n >= K && c->ntiles > 0 && graph_launches(c) > 0;
 }
 
 // The graphs a run of n steps will replay, captured beforehand (so that the
 // capture is not inside a caller's timed region).
 lb_status prepare_graphs(lb_ctx* c, long n) {
     if (!graphs_used(c, n)) return LB_OK;
-    const int launches = c->cfg.graph_steps / steps_per_launch(c->cfg);
-    const int parities = (launches & 1) && n >= 2L * c->cfg.graph_steps ? 2 : 1;
+    const int launches = graph_launches(c);
+    const int parities = (launches & 1) && n >= 2L * launches * steps_per_launch(c) ? 2 : 1;
     for (int q = 0; q < parities; ++q) {
         const int p = c->cur ^ q;
         if (!c->gexec[p])
@@ -585,17 +683,17 @@ lb_status prepare_graphs(lb_ctx* c, long n) {
 }
 
 // readable: leave the state as the read-outs expect it.  They take phi (binary
-// model) from the buffer that the last step read: after a single step that is
-// phi of the state's own time, after a two-step launch the phi of the step
-// before (the one in between stays in LDS).  With two steps per launch the
-// binary model's last step is therefore a single step.
+// model) from the buffer that the last launch read: after a single step that is
+// phi of the state's own time, after a launch of several steps the phi of an
+// earlier one (those in between stay in LDS).  With several steps per launch the
+// binary model's last step is therefore a launch of its own.
 lb_status run_steps(lb_ctx* c, long n, bool readable = true) {
-    const int K = c->cfg.graph_steps;
-    const int spl = steps_per_launch(c->cfg);
-    const bool tail = readable && spl == 2 && c->model == LB_BINARY && n > 0;
+    const int spl = steps_per_launch(c);
+    const bool tail = readable && spl > 1 && c->model == LB_BINARY && n > 0;
     if (tail) --n;
     if (graphs_used(c, n)) {
-        const int launches = K / spl;   // K is even
+        const int launches = graph_launches(c);
+        const int K = launches * spl;
         while (n >= K) {
             if (!c->gexec[c->cur])
                 if (lb_status s = capture_graph(c, c->cur)) return s;
@@ -605,21 +703,13 @@ lb_status run_steps(lb_ctx* c, long n, bool readable = true) {
             n -= K;
         }
     }
-    for (; n >= spl; n -= spl) {
-        enqueue_step(c, false, spl == 2);
+    auto launch = [&](int steps) {
+        enqueue_launch(c, steps);
         c->cur ^= 1;
-        c->t += spl;
-    }
-    if (n > 0) {   // an odd step of a two-step schedule
-        enqueue_step(c, false, false);
-        c->cur ^= 1;
-        c->t += 1;
-    }
-    if (tail) {
-        enqueue_step(c, false, false);
-        c->cur ^= 1;
-        c->t += 1;
-    }
+        c->t += steps;
+    };
+    for (; n > 0; n -= std::min<long>(n, spl)) launch((int)std::min<long>(n, spl));
+    if (tail) launch(1);
     HIP_TRY(hipGetLastError());
     return LB_OK;
 }
@@ -1212,7 +1302,7 @@ lb_status lb_set_launch_config(lb_ctx* c, const lb_launch_config* cfg) {
     if (ch != 0 && (ch < LB_MIN_CHUNK || ch > 4096))
         return fail(LB_EINVAL, "chunk_rows must be 0 or in 4..4096");
     const bool retile = r != c->cfg.tile_rows || cfg->chunk_rows != c->cfg.chunk_rows ||
-                        strip_width(*cfg) != strip_width(c->cfg);
+                        cfg->schedule != c->cfg.schedule;
     c->cfg = *cfg;
     drop_graphs(c);
     if (lb_status s = set_storage(c, cfg->schedule == 6 ? 1 : 0)) return s;
@@ -1260,10 +1350,11 @@ lb_status lb_autotune(lb_ctx* c, int trial_steps, lb_launch_config* best, double
     std::vector<lb_launch_config> cand;
     const int ar = orig.fp64_arith;   // the arithmetic is a choice of the caller, not tuned
     for (int ch : {6, 8, 12, 16, 32}) cand.push_back({orig.tile_rows, 3, 4, 0, ar, ch});
-    for (int ch : {8, 12, 16, 32}) cand.push_back({orig.tile_rows, 4, 4, 0, ar, ch});
-    for (int ch : {8, 12, 16, 24, 32}) cand.push_back({orig.tile_rows, 5, 4, 0, ar, ch});
+    // (the block kernels of schedules 4, van der Waals, and 6 take no chunk height)
     if (c->model == LB_BINARY)
-        for (int ch : {16, 20, 24, 32}) cand.push_back({orig.tile_rows, 6, 4, 0, ar, ch});
+        for (int ch : {8, 12, 16, 32}) cand.push_back({orig.tile_rows, 4, 4, 0, ar, ch});
+    cand.push_back({orig.tile_rows, c->model == LB_BINARY ? 6 : 4, 4, 0, ar, orig.chunk_rows});
+    for (int ch : {8, 12, 16, 24, 32}) cand.push_back({orig.tile_rows, 5, 4, 0, ar, ch});
     for (int r : {4, 8}) {
         cand.push_back({r, 1, 4, 0, ar, orig.chunk_rows});
         cand.push_back({r, 2, 4, 0, ar, orig.chunk_rows});
@@ -1327,6 +1418,7 @@ void lb_free(lb_ctx* c) {
     drop_graphs(c);
     if (c->ev0) (void)hipEventDestroy(c->ev0);
     if (c->ev1) (void)hipEventDestroy(c->ev1);
+    (void)hipFree(c->d_blocks);
     if (c->own_mem && c->mem) (void)hipFree(c->mem);
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
     delete c;

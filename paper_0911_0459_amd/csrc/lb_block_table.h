@@ -1,0 +1,128 @@
+// Tile table of the multi-step block kernels: the output nodes and the region of
+// each workgroup.  Host code only, so that it also builds without HIP.
+#pragma once
+#include <algorithm>
+#include <vector>
+
+#include "lbcap.h"
+
+namespace lbk {
+
+// Output nodes [xs, xe) x [ya, yb) of capillary cap; the workgroup's region
+// starts at row yr and at column xs - 2 K.
+struct BlockDev {
+    int cap;
+    int xs, xe;
+    int ya, yb;
+    int yr;
+};
+
+// Tiles for regions of rx x ry nodes advanced K steps per launch (rx, ry > 4 K);
+// returns their number and lists them if out is given.  A step reaches two nodes,
+// so a tile needs 2 K nodes around it, taken periodically; tiles lie in the tube's
+// channel or in the reservoir, never in both.  Where every column a tile can read
+// lies in the tube, the region ends one wall row outside the channel: nothing
+// behind the wall can reach the tile, so a channel that fits the region between
+// its walls needs no halo rows at all.  Tiles are of balanced height, and of
+// balanced width or, with align > 1, cut at multiples of align columns.  Listed
+// column by column, so that neighbouring tiles are close in the table.
+inline size_t build_blocks(const std::vector<lb_geometry>& G, const std::vector<int>& active, int K, int rx, int ry,
+                           int align, std::vector<BlockDev>* out) {
+    const int halo = 2 * K, wmax = rx - 2 * halo, hmax = ry - 2 * halo;
+    size_t count = 0;
+    if (out) out->clear();
+    for (size_t k = 0; k < G.size(); ++k) {
+        if (!active[k]) continue;
+        const lb_geometry& g = G[k];
+        const bool tube = g.tube_len > 0;
+        const int x0 = tube ? g.x_in : g.nx, x1 = tube ? g.x_in + g.tube_len : g.nx;
+        // n tiles over the H rows from y0; the first and the last one `extra` rows
+        // taller than an equal share
+        auto column = [&](int xs, int xe, int y0, int H, int n, int extra, bool walled) {
+            count += n;
+            if (!out) return;
+            const long long inner = H - 2 * extra;
+            int ya = y0;
+            for (int j = 0; j < n; ++j) {
+                const int yb = j == n - 1 ? y0 + H : y0 + extra + (int)(inner * (j + 1) / n);
+                out->push_back(BlockDev{(int)k, xs, xe, ya, yb, walled && j == 0 ? ya - 1 : ya - halo});
+                ya = yb;
+            }
+        };
+        auto section = [&](int c0, int c1, bool in_tube) {
+            const int w = c1 - c0, n = (w + wmax - 1) / wmax;
+            for (int i = 0, xs = c0, xe; xs < c1; ++i, xs = xe) {
+                xe = align > 1 ? std::min(c1, (xs + wmax) / align * align) : c0 + (int)((long long)w * (i + 1) / n);
+                const int H = g.tube_h;
+                if (!in_tube) {
+                    column(xs, xe, 0, g.ny, (g.ny + hmax - 1) / hmax, 0, false);
+                } else if (g.tube_len < g.nx && (xs - halo < g.x_in || xe + halo > x1)) {
+                    column(xs, xe, g.y0, H, (H + hmax - 1) / hmax, 0, false);
+                } else {
+                    // rows a tile can hold next to one wall: hmax and what the missing halo leaves
+                    const int extra = halo - 1, one = hmax + extra;
+                    if (H <= ry - 2)
+                        column(xs, xe, g.y0, H, 1, 0, true);
+                    else if (H <= 2 * one)
+                        column(xs, xe, g.y0, H, 2, 0, true);
+                    else
+                        column(xs, xe, g.y0, H, 2 + (H - 2 * one + hmax - 1) / hmax, extra, true);
+                }
+            }
+        };
+        section(0, x0, false);
+        section(x0, x1, true);
+        section(x1, g.nx, false);
+    }
+    return count;
+}
+
+// How a context's lattices are cut: a shape (0: 32 x 32 nodes, one node per
+// thread; 1: 64 columns, two nodes per thread, 24 rows for the binary model, 32
+// for van der Waals: what two workgroups per CU leave in LDS) and K.
+struct BlockPlan {
+    int shape, K;
+    size_t tiles;
+};
+
+constexpr int BLOCK_SHAPES = 2;
+inline int block_rx(int shape) { return shape == 0 ? 32 : 64; }
+inline int block_ry(int shape, bool vdw) { return shape == 0 || vdw ? 32 : 24; }
+// Columns the tiles are cut at.  A lattice beyond the caches is bound by the lines
+// its tiles share: whole 64-byte sectors measured 71.9 against 74.0 us per step
+// (vdW 16384 x 1024, K = 4).  The binary tiles (K = 2: 56 columns) would lose more
+// columns than that gains (the 256-capillary sweep: 422 against 374 us).
+inline int block_align(int shape, bool vdw) { return shape == 1 && vdw ? 16 : 1; }
+
+// The cheapest plan.  A launch costs its own latency, which grows with K, and, once
+// every CU has a tile, so much for every further tile per CU.  Both are linear
+// fits (us) to lattices of 1e4 to 3e7 nodes; they hold to 10 - 20 %, which is
+// less than the candidates differ where it matters: small shape and large K while
+// the CUs are idle (binary 256 x 64: 2.6 us a step at K = 6, 3.8 at K = 2), small K
+// when halos cost throughput (binary 4096 x 256: 8.7 us at K = 2, 12.1 at K = 4), the
+// large shape, with fewer halo nodes, from about a million nodes (the
+// 256-capillary sweep: 374 us against 440).
+inline BlockPlan plan_block_tiles(const std::vector<lb_geometry>& G, const std::vector<int>& active, bool vdw) {
+    struct Cost {
+        int shape, kmin, kmax;
+        double launch, launch_k, tile, tile_k;
+    };
+    static const Cost binary[] = {{0, 2, 6, 3.6, 2.1, 1.9, 0.65}, {1, 2, 3, 6.5, 2.4, 3.6, 0.5}};
+    static const Cost van[] = {{0, 2, 6, 3.2, 1.22, 2.4, 0.22}, {1, 2, 4, 3.7, 2.1, 5.9, 0.0}};
+    BlockPlan best{0, 0, 0};
+    double cheapest = 0.0;
+    for (const Cost& c : vdw ? van : binary)
+        for (int K = c.kmin; K <= c.kmax; ++K) {
+            const size_t n = build_blocks(G, active, K, block_rx(c.shape), block_ry(c.shape, vdw),
+                                          block_align(c.shape, vdw), nullptr);
+            const double over = n > 256 ? n / 256.0 - 1.0 : 0.0;
+            const double us = (c.launch + c.launch_k * K + (c.tile + c.tile_k * K) * over) / K;
+            if (best.K == 0 || us < cheapest) {
+                best = BlockPlan{c.shape, K, n};
+                cheapest = us;
+            }
+        }
+    return best;
+}
+
+}  // namespace lbk

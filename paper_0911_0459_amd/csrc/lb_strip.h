@@ -96,9 +96,10 @@ struct LaneCols {
     bool t0, tm, tp;
 };
 
-__device__ __forceinline__ LaneCols lane_cols(const Geo& g, int xl) {
+// c0: the lane's column, 0 <= c0 < nx
+__device__ __forceinline__ LaneCols lane_cols_of(const Geo& g, int c0) {
     LaneCols L;
-    L.c0 = wrap_mod(xl, g.nx);
+    L.c0 = c0;
     L.cm = L.c0 == 0 ? g.nx - 1 : L.c0 - 1;
     L.cp = L.c0 == g.nx - 1 ? 0 : L.c0 + 1;
     L.b0 = 4 * L.c0;
@@ -109,6 +110,8 @@ __device__ __forceinline__ LaneCols lane_cols(const Geo& g, int xl) {
     L.tp = g.tube_col(L.cp);
     return L;
 }
+
+__device__ __forceinline__ LaneCols lane_cols(const Geo& g, int xl) { return lane_cols_of(g, wrap_mod(xl, g.nx)); }
 
 // Row data: wrapped row and neighbours, their offsets, whether they are wall rows.
 struct RowInfo {

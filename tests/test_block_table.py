@@ -1,0 +1,23 @@
+"""The tile table of the multi-step block kernels (host code, built here with
+g++): every fluid node is the output of exactly one tile, no solid node is, and
+each tile's region holds every node and wall its steps can read, for all shapes
+and step counts, on fixed and random geometries."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_tiles_cover_and_regions_reach(tmp_path):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no g++")
+    exe = str(tmp_path / "block_table_check")
+    subprocess.run([gxx, "-std=c++17", "-O2", "-fsanitize=address,undefined", "-D_GLIBCXX_ASSERTIONS",
+                    "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_0911_0459_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "block_table_check.cpp"), "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stdout + r.stderr
