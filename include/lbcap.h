@@ -397,12 +397,9 @@ lb_status mlp_predict(mlp_net* net, const float* X, int n, float* Y);
  * memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid allocation): the same outputs as mlp_predict, from caller-owned
  * DEVICE arrays X (n x 19) and Y (n x 64, written), enqueued on the network's
- * stream without synchronising.  No allocation: the hidden activations live
- * in a static device array of 3 x MLP_NOALLOC_MAX_ROWS x 256 floats (3 MiB)
- * that each GPU holds until the process ends; n above MLP_NOALLOC_MAX_ROWS is
- * rejected with LB_EINVAL.  Every call on one GPU uses the same array, so calls
- * that overlap in time on one GPU (other streams, other threads, other
- * networks) race and must be serialised by the caller. */
+ * stream without synchronising.  No allocation: the hidden activations never
+ * leave the compute units.  n above MLP_NOALLOC_MAX_ROWS is rejected with
+ * LB_EINVAL.  Y may overlap X (one copy of X more, into memory of the network). */
 #define MLP_NOALLOC_MAX_ROWS 1024
 lb_status mlp_predict_device_noalloc(mlp_net* net, const float* X, int n, float* Y);
 /* Mean-squared-error loss and its parameter gradient for n rows (no update);

@@ -2,22 +2,24 @@
 // with GELU activations, trained by mean-squared error and Adam, all on the
 // device in FP32.
 //
-// Every dense product (forward, input gradient, weight gradient) runs through
-// one MFMA kernel: 64 x 64 output tiles per workgroup of four wavefronts, each
-// wavefront a 32 x 32 block of 2 x 2 v_mfma_f32_16x16x4f32 tiles, K staged
-// through LDS 16 at a time.  Operand strides are free, so the transposed
-// products of the backward pass read the stored activations and weights in
-// place.  Bias, GELU and the GELU derivative are fused into the epilogue.
-// Reductions (bias gradients, the loss) are sequential per output element or
-// a fixed tree, so a training run is bitwise reproducible.
+// Two kernels.  mlp_rows takes a few rows through all four layers (and, for the
+// gradient, back again): the activations of the rows stay in LDS and registers,
+// the weights stream through once per direction.  mlp_wgrad forms every weight
+// and bias gradient from the activations and output gradients that mlp_rows left
+// and, in training, applies Adam to them at once.  So a forward pass is one
+// launch and a training step two.
+//
+// Every product runs on FP32 matrix instructions whose accumulation is a chain of
+// fused multiply-adds in the order of k, one rounding each (v_mfma_f32_4x4x1 and
+// 16x16x4 alike), so the results do not depend on how rows are tiled.  Reductions
+// (bias gradients, the loss) are sequential per output element or a fixed tree:
+// a training run is bitwise reproducible.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
-#include <map>
-#include <mutex>
 #include <string>
 #include <vector>
 
@@ -32,184 +34,437 @@ constexpr int WMAX = 256;               // widest layer
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 
-enum Epi { EPI_STORE = 0, EPI_BIAS = 1, EPI_BIAS_GELU = 2, EPI_GELU_BWD = 3 };
+// Packed copies of the weights, kept in step with the parameters: what a lane of
+// mlp_rows multiplies next lies in one 16-byte word, 1 KB per wavefront load.
+//   forward   Wf[l][c / 64][k / 4][c % 64][k % 4] = W_l[c][k]   (c: output, k: input)
+//   backward  Wb[l][c / 64][k / 4][c % 64][k % 4] = W_l[k][c]   (c: input, k: output; l >= 1)
+// The first layer's 19 inputs are padded to 32 with zeros.
+constexpr int KPAD[NLAYER] = {32, 256, 256, 256};
+constexpr int WF_OFF[NLAYER + 1] = {0, 8192, 8192 + 65536, 8192 + 2 * 65536, 8192 + 2 * 65536 + 16384};
+constexpr int WB_OFF[NLAYER + 1] = {0, 0, 65536, 2 * 65536, 2 * 65536 + 16384};
+constexpr int PACKED = WF_OFF[NLAYER] + WB_OFF[NLAYER];
 
-// C(m, n) = sum_k A(m, k) B(k, n) over an M x N x K problem, with
-// A(m, k) = A[m sam + k sak] and B(k, n) = B[k sbk + n sbn]; one of each pair
-// of strides is 1.  Epilogues:
-//   EPI_STORE      C = acc
-//   EPI_BIAS       C = acc + bias[n]
-//   EPI_BIAS_GELU  C = z = acc + bias[n], H = gelu(z)      (H has C's layout)
-//   EPI_GELU_BWD   C = acc * gelu'(Z)                        (Z has C's layout)
-struct GemmArgs {
-    int M, N, K;
-    const float* A;
-    long sam, sak;
-    const float* B;
-    long sbk, sbn;
-    float* C;
-    int ldc;
-    const float* bias;
-    float* H;
-    const float* Z;
+__host__ __device__ constexpr int w_off(int l) {
+    int n = 0;
+    for (int i = 0; i < l; ++i) n += DIMS[i + 1] * DIMS[i] + DIMS[i + 1];
+    return n;
+}
+__host__ __device__ constexpr int b_off(int l) { return w_off(l) + DIMS[l + 1] * DIMS[l]; }
+
+// gelu(z) and its derivative from e1 = 1 + erf(z / sqrt(2)).
+__device__ __forceinline__ float gelu_e1(float z) { return 1.f + erff(z * 0.70710678118654752f); }
+__device__ __forceinline__ float gelu(float z, float e1) { return 0.5f * z * e1; }
+__device__ __forceinline__ float gelu_grad(float z, float e1) {
+    return 0.5f * e1 + z * 0.39894228040143268f * expf(-0.5f * z * z);
+}
+
+// Weight (o, i) of layer l into its packed places.
+__device__ __forceinline__ void pack_weight(float* packed, int l, int o, int i, float w) {
+    packed[WF_OFF[l] + (((o >> 6) * (KPAD[l] >> 2) + (i >> 2)) * 64 + (o & 63)) * 4 + (i & 3)] = w;
+    if (l > 0)
+        packed[WF_OFF[NLAYER] + WB_OFF[l] + (((i >> 6) * (DIMS[l + 1] >> 2) + (o >> 2)) * 64 + (i & 63)) * 4 +
+               (o & 3)] = w;
+}
+
+__global__ void __launch_bounds__(256) mlp_pack(const float* __restrict__ P, float* __restrict__ packed) {
+    const int e = blockIdx.x * 256 + threadIdx.x;
+#pragma unroll
+    for (int l = 0; l < NLAYER; ++l) {
+        const int k = e - w_off(l);
+        if (k >= 0 && k < DIMS[l + 1] * DIMS[l]) pack_weight(packed, l, k / DIMS[l], k % DIMS[l], P[e]);
+    }
+}
+
+// What mlp_rows leaves for mlp_wgrad, in the order in which that kernel's lanes
+// multiply: rows in groups of 16, columns in tiles of 16, and per group and tile
+// [row % 4][column % 16][row / 4 % 4].  Rows past the last one of the pass up to a
+// multiple of 16 are zero in the output gradients and finite in the activations.
+__device__ __forceinline__ long grad_at(int ntile, int group, int tile, int r4, int c) {
+    return ((long)(group * ntile + tile) * 64 + r4 * 16 + c) * 4;
+}
+
+struct RowsArgs {
+    const float* P;         // parameters (the biases are read)
+    const float* packed;
+    const float* X;         // n x 19
+    const int* idx;         // rows of X and Y that the pass takes, null: 0 .. n-1
+    int n;
+    float* out;             // n x 64, or null
+    // gradient pass only
+    const float* Y;         // n x 64 targets
+    float inv;              // 1 / (64 n)
+    float* act[NLAYER];     // layer inputs, packed (grad_at)
+    float* dz[NLAYER];      // gradients of the pre-activations, packed
+    float* loss;            // sum of squared errors, one per workgroup
 };
 
-constexpr int BM = 64, BN = 64, BK = 16, PADL = 4;
-
-__device__ __forceinline__ float gelu(float z) { return 0.5f * z * (1.f + erff(z * 0.70710678118654752f)); }
-
-__device__ __forceinline__ float gelu_grad(float z) {
-    return 0.5f * (1.f + erff(z * 0.70710678118654752f)) + z * 0.39894228040143268f * expf(-0.5f * z * z);
+// Workgroup barrier that orders LDS accesses only: the weights requested ahead stay
+// in flight, and nothing that the kernel stores is read by it.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-template <int EPI>
-__global__ void __launch_bounds__(256) mlp_gemm(GemmArgs g) {
-    __shared__ float As[BK][BM + PADL];   // k-major: a wavefront reads 16 consecutive m
-    __shared__ float Bs[BK][BN + PADL];
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
-    const int wm = (w & 1) * 32, wn = (w >> 1) * 32;
-    const int lr = lane & 15, lk = lane >> 4;
-    f4 acc[2][2];
+// The stream of weights of one wavefront: chunks of 16 k x 64 columns, four 16-byte
+// words per lane, through the four layers and (gradient) back through the last
+// three.  Chunk g is requested AHEAD chunks before it is multiplied, across layers:
+// with one or two wavefronts per SIMD it has to cover the L2's latency by itself
+// (about 1000 cycles; a chunk's arithmetic takes 128 MT, or 256 for MT = 1, whose
+// single chain of products waits for itself).  Left to the compiler, one chunk
+// ahead: 2.5 times as long.
+constexpr int CHUNK0[8] = {0, 2, 18, 34, 50, 54, 70, 86};   // first chunk of each product
+template <bool GRAD, int AHEAD>
+struct Stream {
+    static constexpr int RING = AHEAD + 1;
+    const f4* base[GRAD ? 7 : 4];
+    f4 w[RING][4];
+    __device__ __forceinline__ void init(const float* packed, int wv, int lane) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int l = 0; l < NLAYER; ++l)   // (the 64 outputs are one tile)
+            base[l] = (const f4*)(packed + WF_OFF[l]) + (l < NLAYER - 1 ? wv * (KPAD[l] >> 2) * 64 : 0) + lane;
+        if constexpr (GRAD) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+            for (int l = NLAYER - 1; l > 0; --l)
+                base[NLAYER + (NLAYER - 1 - l)] =
+                    (const f4*)(packed + WF_OFF[NLAYER] + WB_OFF[l]) + wv * (DIMS[l + 1] >> 2) * 64 + lane;
+        }
+#pragma unroll
+        for (int g = 0; g < AHEAD; ++g) request(g);
+    }
+    // (g is a constant wherever this is called)
+    __device__ __forceinline__ void request(int g) {
+        constexpr int NP = GRAD ? 7 : 4;
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+            if (g >= CHUNK0[p] && g < CHUNK0[p + 1]) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) w[g % RING][q] = base[p][((g - CHUNK0[p]) * 4 + q) * 64];
+            }
+    }
+};
 
-    for (int k0 = 0; k0 < g.K; k0 += BK) {
+// acc[m][v] += sum over k of H(4 m + v, k) W(column of the lane, k), in the order of k:
+// product P of the stream.  Hs: [m][k][4 rows] in LDS, WMAX k apart.  The 4x4x1
+// instruction works on 16 blocks of 4 rows x 4 columns; with the first operand
+// broadcast from block k % 16, one LDS word per lane holds 4 rows of 16 k.
+template <int MT, int P, bool GRAD, int AHEAD>
+__device__ __forceinline__ void rows_product(Stream<GRAD, AHEAD>& s, const float* Hs, int lane, f4 (&acc)[MT]) {
+    constexpr int NC = CHUNK0[P + 1] - CHUNK0[P];
+    float a[2][MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) a[0][m] = Hs[m * WMAX * 4 + lane];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        const int g = CHUNK0[P] + c;
+        s.request(g + AHEAD);
+        if (c + 1 < NC) {
+#pragma unroll
+            for (int m = 0; m < MT; ++m) a[(c + 1) & 1][m] = Hs[(m * WMAX + (c + 1) * 16) * 4 + lane];
+        }
+        // (the requests stay ahead of the arithmetic)
+        __builtin_amdgcn_sched_barrier(0);
+#define MLP_STEP(k)                                                                                       \
+    _Pragma("unroll") for (int m = 0; m < MT; ++m) acc[m] =                                               \
+        __builtin_amdgcn_mfma_f32_4x4x1f32(a[c & 1][m], s.w[g % (AHEAD + 1)][(k) / 4][(k) % 4], acc[m], 4, k, 0);
+        MLP_STEP(0) MLP_STEP(1) MLP_STEP(2) MLP_STEP(3) MLP_STEP(4) MLP_STEP(5) MLP_STEP(6) MLP_STEP(7)
+        MLP_STEP(8) MLP_STEP(9) MLP_STEP(10) MLP_STEP(11) MLP_STEP(12) MLP_STEP(13) MLP_STEP(14) MLP_STEP(15)
+#undef MLP_STEP
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// 4 MT rows through the network: four wavefronts, each 64 of the 256 columns of a
+// hidden layer (the 64 outputs: one wavefront per 4 rows).  GRAD: and back again.
+// Bound by the chain of products per column (787 forward, 1363 with the gradient) and
+// the weights' way through the CU (0.6 and 1.2 MB per workgroup), both about 10 us a
+// gradient pass; the activation functions add a third.  A training step of 512 rows takes
+// 28 us (22 launches took 860), the gradient of 3675 rows 63 us (5800).
+template <int MT, bool GRAD>
+__global__ void __launch_bounds__(256, GRAD && MT == 2 ? 2 : 1) mlp_rows(RowsArgs a) {
+    constexpr int R = 4 * MT;
+    __shared__ float Hb[2][MT * WMAX * 4];   // activations of the rows, [m][k][4 rows], two layers in turn
+    const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6), col = t;
+    const int r0 = blockIdx.x * R;
+    // group of 16 rows and this workgroup's first fours of it, for the packed outputs
+    const int group = r0 >> 4, f0 = (r0 & 15) >> 2;
+    auto row_of = [&](int r) { return a.idx ? a.idx[r] : r; };
+    // the rows of X, zero past the last row and the last input (before the weights, or
+    // they wait for all of those requested ahead)
+    constexpr int XN = (R * 32 + 255) / 256;
+    float xv[XN];
+#pragma unroll
+    for (int j = 0; j < XN; ++j) {
+        const int e = t + 256 * j, r = e >> 5, k = e & 31;
+        xv[j] = (r < R && k < DIMS[0] && r0 + r < a.n) ? a.X[(long)row_of(r0 + r) * DIMS[0] + k] : 0.f;
+    }
+    Stream<GRAD, GRAD && MT == 2 ? 4 : 7> ws;
+    ws.init(a.packed, wv, lane);
+#pragma unroll
+    for (int j = 0; j < XN; ++j) {
+        const int e = t + 256 * j, r = e >> 5, k = e & 31;
+        if (r < R) {
+            Hb[0][((r >> 2) * WMAX + k) * 4 + (r & 3)] = xv[j];
+            if (GRAD) a.act[0][grad_at(2, group, k >> 4, r & 3, k & 15) + f0 + (r >> 2)] = xv[j];
+        }
+    }
+    lds_barrier();
+
+    // values of the lane's column and the workgroup's rows to a packed matrix of ntile tiles
+    auto put = [&](float* dst, int ntile, int c, const f4 (&v)[MT]) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int e = t + 256 * r;
-            int m, k;
-            if (g.sak == 1) { m = e >> 4; k = e & 15; } else { m = e & 63; k = e >> 6; }
-            const int gm = m0 + m, gk = k0 + k;
-            As[k][m] = (gm < g.M && gk < g.K) ? g.A[gm * g.sam + gk * g.sak] : 0.f;
-            int n, kb;
-            if (g.sbn == 1) { n = e & 63; kb = e >> 6; } else { n = e >> 4; kb = e & 15; }
-            const int gn = n0 + n, gkb = k0 + kb;
-            Bs[kb][n] = (gn < g.N && gkb < g.K) ? g.B[gkb * g.sbk + gn * g.sbn] : 0.f;
+            float* p = dst + grad_at(ntile, group, c >> 4, r, c & 15) + f0;
+#pragma unroll
+            for (int m = 0; m < MT; ++m) p[m] = v[m][r];
         }
-        __syncthreads();
+    };
+    f4 gp[GRAD ? NLAYER - 1 : 1][MT];   // gelu' of the hidden pre-activations
+    int cur = 0;
 #pragma unroll
-        for (int kk = 0; kk < BK; kk += 4) {
-            float a[2], b[2];
+    for (int l = 0; l < NLAYER - 1; ++l) {
+        f4 acc[MT];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) a[i] = As[kk + lk][wm + 16 * i + lr];
+        for (int m = 0; m < MT; ++m) acc[m] = f4{0.f, 0.f, 0.f, 0.f};
+        const float bias = a.P[b_off(l) + col];
+        if (l == 0)
+            rows_product<MT, 0>(ws, Hb[cur], lane, acc);
+        else if (l == 1)
+            rows_product<MT, 1>(ws, Hb[cur], lane, acc);
+        else
+            rows_product<MT, 2>(ws, Hb[cur], lane, acc);
+        f4 h[MT];
 #pragma unroll
-            for (int j = 0; j < 2; ++j) b[j] = Bs[kk + lk][wn + 16 * j + lr];
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-        __syncthreads();
-    }
-    // 16 x 16 result tile: lane holds rows 4 (lane / 16) + v, column lane % 16
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int m = 0; m < MT; ++m) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int m = m0 + wm + 16 * i + 4 * lk + v;
-                const int n = n0 + wn + 16 * j + lr;
-                if (m >= g.M || n >= g.N) continue;
-                const long o = (long)m * g.ldc + n;
-                const float x = acc[i][j][v];
-                if (EPI == EPI_STORE) {
-                    g.C[o] = x;
-                } else if (EPI == EPI_BIAS) {
-                    g.C[o] = x + g.bias[n];
-                } else if (EPI == EPI_BIAS_GELU) {
-                    const float z = x + g.bias[n];
-                    g.C[o] = z;
-                    g.H[o] = gelu(z);
-                } else {
-                    g.C[o] = x * gelu_grad(g.Z[o]);
+                const float z = acc[m][v] + bias;
+                const float e1 = gelu_e1(z);
+                h[m][v] = gelu(z, e1);
+                if (GRAD) gp[l][m][v] = gelu_grad(z, e1);
+            }
+            *(f4*)&Hb[cur ^ 1][(m * WMAX + col) * 4] = h[m];
+        }
+        if (GRAD) put(a.act[l + 1], 16, col, h);
+        lds_barrier();
+        cur ^= 1;
+    }
+    // outputs, 64 columns: wavefront w takes the four rows w % MT (with fewer fours than
+    // wavefronts the others do the same work and leave no result)
+    float se = 0.f;
+    {
+        constexpr int L3 = NLAYER - 1;
+        const int m = wv % MT;
+        f4 acc[1] = {f4{0.f, 0.f, 0.f, 0.f}};
+        const float bias = a.P[b_off(L3) + lane];
+        float y[4] = {0.f, 0.f, 0.f, 0.f};
+        if (GRAD) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int r = r0 + 4 * m + v;
+                if (r < a.n) y[v] = a.Y[(long)row_of(r) * DIMS[NLAYER] + lane];
+            }
+        }
+        rows_product<1, 3>(ws, &Hb[cur][m * WMAX * 4], lane, acc);
+        if (wv < MT) {
+            f4 dz;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int r = r0 + 4 * m + v;
+                const float o = acc[0][v] + bias;
+                if (a.out && r < a.n) a.out[(long)r * DIMS[NLAYER] + lane] = o;
+                if (GRAD) {
+                    const float d = r < a.n ? o - y[v] : 0.f;
+                    dz[v] = 2.f * d * a.inv;
+                    se += d * d;
+                    a.dz[L3][grad_at(4, group, lane >> 4, v, lane & 15) + f0 + m] = dz[v];
                 }
             }
-}
-
-// db[j] = sum over rows of dZ[r][j], rows in order.
-__global__ void mlp_bias_grad(const float* __restrict__ dZ, int rows, int cols, float* __restrict__ db) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= cols) return;
-    float s = 0.f;
-    for (int r = 0; r < rows; ++r) s += dZ[(long)r * cols + j];
-    db[j] = s;
-}
-
-// Mean-squared error over rows x cols: dOut = 2 (out - y) / (rows cols) and
-// loss = mean (out - y)^2, by one workgroup with a fixed reduction tree.
-__global__ void __launch_bounds__(256) mlp_mse(const float* __restrict__ out, const float* __restrict__ y,
-                                               long count, float* __restrict__ dout, float* __restrict__ loss) {
-    __shared__ float red[256];
-    const int t = threadIdx.x;
-    const float inv = 1.f / (float)count;
-    float s = 0.f;
-    for (long e = t; e < count; e += 256) {
-        const float d = out[e] - y[e];
-        dout[e] = 2.f * d * inv;
-        s += d * d;
+            if (GRAD) *(f4*)&Hb[cur ^ 1][(m * WMAX + lane) * 4] = dz;
+        }
     }
-    red[t] = s;
-    __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if (t < h) red[t] += red[t + h];
-        __syncthreads();
+    if constexpr (GRAD) {
+        // squared errors: a fixed tree over the lanes, then the wavefronts in order
+        __shared__ float red[4];
+        for (int s = 32; s > 0; s >>= 1) se += __shfl_down(se, s);
+        if (lane == 0) red[wv] = se;
+        lds_barrier();
+        if (t == 0) a.loss[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
+        cur ^= 1;
+#pragma unroll
+        for (int l = NLAYER - 1; l > 0; --l) {
+            // d act = dz W, times gelu' of the layer below
+            f4 acc[MT];
+#pragma unroll
+            for (int m = 0; m < MT; ++m) acc[m] = f4{0.f, 0.f, 0.f, 0.f};
+            if (l == 3)
+                rows_product<MT, 4>(ws, Hb[cur], lane, acc);
+            else if (l == 2)
+                rows_product<MT, 5>(ws, Hb[cur], lane, acc);
+            else
+                rows_product<MT, 6>(ws, Hb[cur], lane, acc);
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                acc[m] *= gp[l - 1][m];
+                if (l > 1) *(f4*)&Hb[cur ^ 1][(m * WMAX + col) * 4] = acc[m];
+            }
+            put(a.dz[l - 1], 16, col, acc);
+            if (l > 1) lds_barrier();
+            cur ^= 1;
+        }
     }
-    if (t == 0) *loss = red[0] * inv;
 }
 
 // Adam (Kingma & Ba 2015, Algorithm 1); bc1 = 1 - beta1^t, bc2 = 1 - beta2^t.
-__global__ void mlp_adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                         float* __restrict__ v, long count, float lr, float b1, float b2, float eps, float bc1,
-                         float bc2) {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= count) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.f - b1) * gi;
-    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    p[i] -= lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
+struct AdamArgs {
+    float *P, *m, *v, *packed;
+    float lr, b1, b2, eps, bc1, bc2;
+};
+
+// One parameter: its value and moments before the step, and the gradient.  (Written
+// as fused operations, so that the trained weights do not depend on which products
+// a compiler contracts.)
+struct AdamState {
+    float p, m, v;
+};
+__device__ __forceinline__ AdamState adam_state(const AdamArgs& a, int i) { return AdamState{a.P[i], a.m[i], a.v[i]}; }
+__device__ __forceinline__ float adam(const AdamArgs& a, int i, const AdamState& s, float gi) {
+    const float mi = __builtin_fmaf(1.f - a.b1, gi, a.b1 * s.m);
+    const float vi = __builtin_fmaf(gi, (1.f - a.b2) * gi, a.b2 * s.v);
+    a.m[i] = mi;
+    a.v[i] = vi;
+    const float p = s.p - a.lr * (mi / a.bc1) / (sqrtf(vi / a.bc2) + a.eps);
+    a.P[i] = p;
+    return p;
 }
 
-// Rows idx[r] of X (cols_x wide) and Y (cols_y wide) into Xb, Yb.
-__global__ void mlp_gather(const float* __restrict__ X, const float* __restrict__ Y, const int* __restrict__ idx,
-                           int rows, int cols_x, int cols_y, float* __restrict__ Xb, float* __restrict__ Yb) {
-    const int r = blockIdx.x;
-    if (r >= rows) return;
-    const long src = idx[r];
-    for (int c = threadIdx.x; c < cols_x; c += blockDim.x) Xb[(long)r * cols_x + c] = X[src * cols_x + c];
-    for (int c = threadIdx.x; c < cols_y; c += blockDim.x) Yb[(long)r * cols_y + c] = Y[src * cols_y + c];
+struct WgradArgs {
+    const float* act[NLAYER];
+    const float* dz[NLAYER];
+    int groups;             // groups of 16 rows
+    const float* part;      // squared errors of the workgroups of mlp_rows
+    int nparts;
+    float inv;
+    float* loss;
+    float* G;               // gradients (null in training)
+    AdamArgs adam;
+};
+
+constexpr int WG_TILES[NLAYER] = {8, 64, 64, 16};   // 32 x 32 tiles of weight gradients per layer
+constexpr int WG_WEIGHTS = 8 + 64 + 64 + 16;
+constexpr int WG_BIAS = (3 * 16 + 4) / 4;           // workgroups of the bias gradients
+constexpr int WG_GRID = WG_WEIGHTS + WG_BIAS + 1;   // and one for the loss
+
+// Sum over the rows of A(row, o) B(row, i) of one 16 x 16 tile, rows in order; ONES: of
+// A(row, o).  16 groups of rows are requested ahead: one wavefront per SIMD, and what
+// mlp_rows wrote comes from beyond the L2 for most of the XCDs.
+template <bool ONES>
+__device__ __forceinline__ f4 wgrad_sum(const f4* __restrict__ A, int sa, const f4* __restrict__ B, int sb,
+                                        int groups) {
+    constexpr int DEPTH = 16;
+    f4 acc = {0.f, 0.f, 0.f, 0.f};
+    f4 x[DEPTH], y[DEPTH];
+    auto request = [&](int d, int g) {
+        const int gg = min(g, groups - 1);   // (past the end: a repeat, unused)
+        x[d] = A[(long)gg * sa];
+        if (!ONES) y[d] = B[(long)gg * sb];
+    };
+    auto add = [&](int d) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[d][q], ONES ? 1.f : y[d][q], acc, 0, 0, 0);
+    };
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) request(d, d);
+    int g = 0;
+    for (; g + DEPTH <= groups; g += DEPTH) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            add(d);
+            request(d, g + DEPTH + d);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d)
+        if (g + d < groups) add(d);
+    return acc;
 }
 
-// ---- allocation-free inference scratch ------------------------------------------
-// Activations of mlp_predict_device_noalloc: one buffer for the pre-activations
-// the forward pass writes but inference does not read, and two that the hidden
-// activations alternate between, each MLP_NOALLOC_MAX_ROWS x 256 floats
-// (3 MiB in all).  Every GPU that runs the library holds its own copy until
-// the process ends; host code addresses it only through the pointer that
-// hipGetSymbolAddress returned for that GPU (noalloc_scratch below).
-constexpr int SCRATCH_BUFS = 3;
-constexpr long SCRATCH_BUF = (long)MLP_NOALLOC_MAX_ROWS * WMAX;
-static __device__ __align__(256) float scratch[SCRATCH_BUFS * SCRATCH_BUF];
+// Gradient of one 16 x 16 tile of dW[o][i] = sum over the rows of dz[r][o] act[r][i] per
+// wavefront, rows in order; the bias gradients are the same sums against ones.
+// A chain of 8 cycles a row per tile, and no more than 660 tiles: bound by that chain.
+// TRAIN: Adam on the finished gradients.
+template <bool TRAIN>
+__global__ void __launch_bounds__(256) mlp_wgrad(WgradArgs a) {
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int b = blockIdx.x, l, ot, it = 0, ni = 0;
+    bool bias = false;
+    if (b >= WG_WEIGHTS + WG_BIAS) {   // the loss
+        float s = 0.f;
+        __shared__ float red[256];
+        for (int e = threadIdx.x; e < a.nparts; e += 256) s += a.part[e];
+        red[threadIdx.x] = s;
+        __syncthreads();
+        for (int h = 128; h > 0; h >>= 1) {
+            if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) *a.loss = red[0] * a.inv;
+        return;
+    }
+    if (b >= WG_WEIGHTS) {
+        bias = true;
+        const int k = (b - WG_WEIGHTS) * 4 + wv;
+        l = k >> 4;
+        ot = k & 15;
+    } else {
+        l = 0;
+#pragma unroll
+        for (int q = 0; q < NLAYER - 1; ++q)
+            if (l == q && b >= WG_TILES[q]) {
+                b -= WG_TILES[q];
+                l = q + 1;
+            }
+        ni = l == 0 ? 2 : 16;               // tiles of 16 inputs
+        const int bi = ni >> 1;
+        ot = (b / bi) * 2 + (wv >> 1);
+        it = (b % bi) * 2 + (wv & 1);
+    }
+    const int no = l == NLAYER - 1 ? 4 : 16;
+    // 16 x 16 result tile: lane holds rows 4 (lane / 16) + v, column lane % 16; a bias
+    // gradient is in every column
+    const int in = DIMS[l], i = it * 16 + (lane & 15), o0 = ot * 16 + 4 * (lane >> 4);
+    const bool mine = bias ? (lane & 15) == 0 : i < in;
+    const int e0 = bias ? b_off(l) + o0 : w_off(l) + o0 * in + i, es = bias ? 1 : in;
+    AdamState state[4];
+    if (TRAIN && mine) {   // (before the sums, which cover the latency)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) state[v] = adam_state(a.adam, e0 + v * es);
+    }
+    const f4* A = (const f4*)a.dz[l] + ot * 64 + lane;
+    const int sa = no * 64;
+    f4 acc;
+    if (bias)
+        acc = wgrad_sum<true>(A, sa, A, sa, a.groups);
+    else
+        acc = wgrad_sum<false>(A, sa, (const f4*)a.act[l] + it * 64 + lane, ni * 64, a.groups);
+    if (!mine) return;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int e = e0 + v * es;
+        if (TRAIN) {
+            const float p = adam(a.adam, e, state[v], acc[v]);
+            if (!bias) pack_weight(a.adam.packed, l, o0 + v, i, p);
+        } else {
+            a.G[e] = acc[v];
+        }
+    }
+}
 
 // ---- host side -----------------------------------------------------------------
 
-long param_count() {
-    long n = 0;
-    for (int l = 0; l < NLAYER; ++l) n += (long)DIMS[l + 1] * DIMS[l] + DIMS[l + 1];
-    return n;
-}
-
-long w_off(int l) {
-    long n = 0;
-    for (int i = 0; i < l; ++i) n += (long)DIMS[i + 1] * DIMS[i] + DIMS[i + 1];
-    return n;
-}
-long b_off(int l) { return w_off(l) + (long)DIMS[l + 1] * DIMS[l]; }
+long param_count() { return w_off(NLAYER); }
 
 uint64_t splitmix64(uint64_t x) {
     x += 0x9E3779B97F4A7C15ull;
@@ -235,16 +490,19 @@ struct mlp_net {
     int device = -1;           // the GPU the parameters live on
     hipStream_t stream = nullptr;
     float* P = nullptr;        // parameters, mlp_get_params layout
-    float* G = nullptr;        // gradients, same layout
+    float* packed = nullptr;   // the weights as mlp_rows reads them
+    float* G = nullptr;        // gradients, mlp_get_params layout
     float* Mo = nullptr;       // Adam first moments
     float* Vo = nullptr;       // Adam second moments
+    float* xcopy = nullptr;    // MLP_NOALLOC_MAX_ROWS rows of X (see mlp_predict_device_noalloc)
     long adam_t = 0;           // Adam steps taken
-    int cap = 0;               // rows the activation buffers hold
-    float* act[NLAYER] = {};   // layer inputs: act[0] = X, act[l] = gelu(z[l-1])
-    float* z[NLAYER] = {};     // pre-activations; z[3] is the output
-    float* d0 = nullptr;       // gradient buffers (ping-pong), cap x WMAX
-    float* d1 = nullptr;
-    float* yb = nullptr;       // targets of the current rows
+    int cap = 0;               // rows that x and y hold
+    float* x = nullptr;        // inputs, cap x 19
+    float* y = nullptr;        // outputs or targets, cap x 64
+    int gcap = 0;              // groups of 16 rows that the packed matrices hold
+    float* act[NLAYER] = {};   // layer inputs, packed
+    float* dz[NLAYER] = {};    // gradients of the pre-activations, packed
+    float* part = nullptr;     // squared errors per workgroup of mlp_rows
     float* loss = nullptr;     // device scalars, one per minibatch
     int loss_cap = 0;
     float* Xall = nullptr;     // training set on the device
@@ -256,151 +514,127 @@ struct mlp_net {
 namespace {
 
 void free_rows(mlp_net* n) {
+    (void)hipFree(n->x);
+    (void)hipFree(n->y);
+    n->x = n->y = nullptr;
+    n->cap = 0;
+}
+
+void free_groups(mlp_net* n) {
     for (int l = 0; l < NLAYER; ++l) {
         (void)hipFree(n->act[l]);
-        (void)hipFree(n->z[l]);
-        n->act[l] = n->z[l] = nullptr;
+        (void)hipFree(n->dz[l]);
+        n->act[l] = n->dz[l] = nullptr;
     }
-    (void)hipFree(n->d0);
-    (void)hipFree(n->d1);
-    (void)hipFree(n->yb);
-    n->d0 = n->d1 = n->yb = nullptr;
-    n->cap = 0;
+    (void)hipFree(n->part);
+    n->part = nullptr;
+    n->gcap = 0;
 }
 
 lb_status ensure_rows(mlp_net* n, int rows) {
     if (rows <= n->cap) return LB_OK;
     MLP_TRY(hipStreamSynchronize(n->stream));
     free_rows(n);
-    for (int l = 0; l < NLAYER; ++l) {
-        MLP_TRY(hipMalloc(&n->act[l], sizeof(float) * (size_t)rows * DIMS[l]));
-        MLP_TRY(hipMalloc(&n->z[l], sizeof(float) * (size_t)rows * DIMS[l + 1]));
-    }
-    MLP_TRY(hipMalloc(&n->d0, sizeof(float) * (size_t)rows * WMAX));
-    MLP_TRY(hipMalloc(&n->d1, sizeof(float) * (size_t)rows * WMAX));
-    MLP_TRY(hipMalloc(&n->yb, sizeof(float) * (size_t)rows * DIMS[NLAYER]));
+    MLP_TRY(hipMalloc(&n->x, sizeof(float) * (size_t)rows * DIMS[0]));
+    MLP_TRY(hipMalloc(&n->y, sizeof(float) * (size_t)rows * DIMS[NLAYER]));
     n->cap = rows;
     return LB_OK;
 }
 
-template <int EPI>
-lb_status gemm(hipStream_t s, const GemmArgs& g) {
-    if (g.M <= 0 || g.N <= 0) return LB_OK;
-    dim3 grid((g.M + BM - 1) / BM, (g.N + BN - 1) / BN);
-    hipLaunchKernelGGL(mlp_gemm<EPI>, grid, dim3(256), 0, s, g);
+// Packed matrices of a gradient pass over `rows` rows.
+lb_status ensure_groups(mlp_net* n, int rows) {
+    const int groups = rows / 16 + (rows % 16 != 0);
+    if (groups <= n->gcap) return LB_OK;
+    MLP_TRY(hipStreamSynchronize(n->stream));
+    free_groups(n);
+    for (int l = 0; l < NLAYER; ++l) {
+        MLP_TRY(hipMalloc(&n->act[l], sizeof(float) * 16 * (size_t)groups * KPAD[l]));
+        MLP_TRY(hipMalloc(&n->dz[l], sizeof(float) * 16 * (size_t)groups * DIMS[l + 1]));
+    }
+    MLP_TRY(hipMalloc(&n->part, sizeof(float) * 4 * (size_t)groups));
+    n->gcap = groups;
+    return LB_OK;
+}
+
+template <int MT, bool GRAD>
+void launch_rows(const mlp_net* net, const RowsArgs& a, int work) {
+    hipLaunchKernelGGL((mlp_rows<MT, GRAD>), dim3(work), dim3(256), 0, net->stream, a);
+}
+
+// Forward pass of n rows of X into out.  Rows per workgroup: 4 are the matrix
+// instruction's least and leave every product a single chain (10 us, of which 4 are
+// the launch's), 8 run two chains in the same time per workgroup, 16 share each
+// weight among most rows.  Measured, us, with 4 / 8 / 16 rows: 17.7 / 13.6 / 19.6 at
+// 1100 rows, 19.4 / 14.4 / 19.3 at 2048, 35.2 / 23.4 / 21.2 at 4096, 128 / 80 / 66 at
+// 16384 (four products as launches of their own: 22 us each at 507 rows).
+lb_status forward(const mlp_net* net, const float* X, int n, float* out) {
+    RowsArgs a{};
+    a.P = net->P;
+    a.packed = net->packed;
+    a.X = X;
+    a.n = n;
+    a.out = out;
+    if (n <= 1024)
+        launch_rows<1, false>(net, a, (n + 3) / 4);
+    else if (n <= 2048)
+        launch_rows<2, false>(net, a, (n + 7) / 8);
+    else
+        launch_rows<4, false>(net, a, n / 16 + (n % 16 != 0));
     MLP_TRY(hipGetLastError());
     return LB_OK;
 }
 
-// Forward pass of `rows` rows with parameters P on stream s: layer l reads
-// in[l] and writes its pre-activation to z[l] and (hidden layers) its GELU to
-// in[l + 1]; z[NLAYER-1] receives the output.
-lb_status forward_bufs(hipStream_t s, const float* P, int rows, const float* const (&in)[NLAYER],
-                       float* const (&z)[NLAYER]) {
+// Loss and gradient of n rows (idx: those rows of X and Y); train: and one Adam
+// step with its result, else the gradient into G.
+lb_status gradient(mlp_net* net, const float* X, const float* Y, const int* idx, int n, float* loss, bool train,
+                   float lr) {
+    RowsArgs a{};
+    a.P = net->P;
+    a.packed = net->packed;
+    a.X = X;
+    a.Y = Y;
+    a.idx = idx;
+    a.n = n;
+    a.inv = 1.f / (float)((long)n * DIMS[NLAYER]);
+    WgradArgs w{};
     for (int l = 0; l < NLAYER; ++l) {
-        const int ni = DIMS[l], no = DIMS[l + 1];
-        GemmArgs g{};
-        g.M = rows;
-        g.N = no;
-        g.K = ni;
-        g.A = in[l];
-        g.sam = ni;
-        g.sak = 1;
-        g.B = P + w_off(l);   // B(k, j) = W[j][k]
-        g.sbk = 1;
-        g.sbn = ni;
-        g.C = z[l];
-        g.ldc = no;
-        g.bias = P + b_off(l);
-        lb_status st;
-        if (l + 1 < NLAYER) {
-            g.H = const_cast<float*>(in[l + 1]);
-            st = gemm<EPI_BIAS_GELU>(s, g);
-        } else {
-            st = gemm<EPI_BIAS>(s, g);
-        }
-        if (st) return st;
+        w.act[l] = a.act[l] = net->act[l];
+        w.dz[l] = a.dz[l] = net->dz[l];
     }
+    a.loss = net->part;
+    w.groups = n / 16 + (n % 16 != 0);
+    w.part = net->part;
+    w.inv = a.inv;
+    w.loss = loss;
+    // Whole groups of 16 rows, as the packed matrices.  4 rows per workgroup while they
+    // leave CUs idle (512 rows: 19.6 against 20.3 us), else 8, two workgroups per CU
+    // (3675 rows: 39.7 us; 64 with 4 rows, 39.9 with 16).
+    if (n <= 1024) {
+        w.nparts = 4 * w.groups;
+        launch_rows<1, true>(net, a, w.nparts);
+    } else {
+        w.nparts = 2 * w.groups;
+        launch_rows<2, true>(net, a, w.nparts);
+    }
+    MLP_TRY(hipGetLastError());
+    if (train) {
+        net->adam_t += 1;
+        const float bc1 = 1.f - (float)std::pow(0.9, (double)net->adam_t);
+        const float bc2 = 1.f - (float)std::pow(0.999, (double)net->adam_t);
+        w.adam = AdamArgs{net->P, net->Mo, net->Vo, net->packed, lr, 0.9f, 0.999f, 1e-8f, bc1, bc2};
+        hipLaunchKernelGGL(mlp_wgrad<true>, dim3(WG_GRID), dim3(256), 0, net->stream, w);
+    } else {
+        w.G = net->G;
+        hipLaunchKernelGGL(mlp_wgrad<false>, dim3(WG_GRID), dim3(256), 0, net->stream, w);
+    }
+    MLP_TRY(hipGetLastError());
     return LB_OK;
 }
 
-// Forward pass of `rows` rows of act[0]; output in z[NLAYER-1].
-lb_status forward(mlp_net* n, int rows) {
-    const float* const in[NLAYER] = {n->act[0], n->act[1], n->act[2], n->act[3]};
-    float* const z[NLAYER] = {n->z[0], n->z[1], n->z[2], n->z[3]};
-    return forward_bufs(n->stream, n->P, rows, in, z);
-}
-
-// Device address of this GPU's copy of `scratch`, resolved once per device
-// (with that device current) by hipGetSymbolAddress: the array's name in host
-// code is a host-side stand-in, not a device address.
-std::mutex g_scratch_mu;
-std::map<int, float*> g_scratch_ptr;
-
-lb_status noalloc_scratch(int device, float** out) {
-    std::lock_guard<std::mutex> lk(g_scratch_mu);
-    auto it = g_scratch_ptr.find(device);
-    if (it != g_scratch_ptr.end()) {
-        *out = it->second;
-        return LB_OK;
-    }
-    int cur = -1;
-    MLP_TRY(hipGetDevice(&cur));
-    if (cur != device) return lbk::set_error(LB_ESTATE, "the network's device is not the current device");
-    void* p = nullptr;
-    MLP_TRY(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
-    g_scratch_ptr[device] = (float*)p;
-    *out = (float*)p;
-    return LB_OK;
-}
-
-// Backward pass from dOut (in d0, rows x 64) into G.
-lb_status backward(mlp_net* n, int rows) {
-    float* dz = n->d0;
-    float* dn = n->d1;
-    for (int l = NLAYER - 1; l >= 0; --l) {
-        const int in = DIMS[l], out = DIMS[l + 1];
-        // dW[o][i] = sum_r dz[r][o] act[r][i]
-        GemmArgs gw{};
-        gw.M = out;
-        gw.N = in;
-        gw.K = rows;
-        gw.A = dz;
-        gw.sam = 1;
-        gw.sak = out;
-        gw.B = n->act[l];
-        gw.sbk = in;
-        gw.sbn = 1;
-        gw.C = n->G + w_off(l);
-        gw.ldc = in;
-        if (lb_status st = gemm<EPI_STORE>(n->stream, gw)) return st;
-        hipLaunchKernelGGL(mlp_bias_grad, dim3((out + 255) / 256), dim3(256), 0, n->stream, dz, rows, out,
-                           n->G + b_off(l));
-        MLP_TRY(hipGetLastError());
-        if (l == 0) break;
-        // d act[r][i] = sum_o dz[r][o] W[o][i], times gelu'(z[l-1][r][i])
-        GemmArgs gx{};
-        gx.M = rows;
-        gx.N = in;
-        gx.K = out;
-        gx.A = dz;
-        gx.sam = out;
-        gx.sak = 1;
-        gx.B = n->P + w_off(l);
-        gx.sbk = in;
-        gx.sbn = 1;
-        gx.C = dn;
-        gx.ldc = in;
-        gx.Z = n->z[l - 1];
-        if (lb_status st = gemm<EPI_GELU_BWD>(n->stream, gx)) return st;
-        std::swap(dz, dn);
-    }
-    return LB_OK;
-}
-
-lb_status mse(mlp_net* n, int rows, float* loss_slot) {
-    hipLaunchKernelGGL(mlp_mse, dim3(1), dim3(256), 0, n->stream, n->z[NLAYER - 1], n->yb,
-                       (long)rows * DIMS[NLAYER], n->d0, loss_slot);
+// The packed weights from the parameters.
+lb_status pack(mlp_net* n) {
+    hipLaunchKernelGGL(mlp_pack, dim3((unsigned)((param_count() + 255) / 256)), dim3(256), 0, n->stream, n->P,
+                       n->packed);
     MLP_TRY(hipGetLastError());
     return LB_OK;
 }
@@ -410,6 +644,7 @@ lb_status ensure_loss(mlp_net* n, int count) {
     MLP_TRY(hipStreamSynchronize(n->stream));
     (void)hipFree(n->loss);
     n->loss = nullptr;
+    n->loss_cap = 0;
     MLP_TRY(hipMalloc(&n->loss, sizeof(float) * (size_t)count));
     n->loss_cap = count;
     return LB_OK;
@@ -441,7 +676,9 @@ lb_status mlp_init(mlp_net** out, int seed, void* hip_stream) {
         return st;
     };
     if (hipMalloc(&n->P, sizeof(float) * np) != hipSuccess || hipMalloc(&n->G, sizeof(float) * np) != hipSuccess ||
-        hipMalloc(&n->Mo, sizeof(float) * np) != hipSuccess || hipMalloc(&n->Vo, sizeof(float) * np) != hipSuccess)
+        hipMalloc(&n->Mo, sizeof(float) * np) != hipSuccess || hipMalloc(&n->Vo, sizeof(float) * np) != hipSuccess ||
+        hipMalloc(&n->packed, sizeof(float) * PACKED) != hipSuccess ||
+        hipMalloc(&n->xcopy, sizeof(float) * MLP_NOALLOC_MAX_ROWS * DIMS[0]) != hipSuccess)
         return bail(lbk::set_error(LB_ENOMEM, "device allocation of the network failed"));
     // uniform(-1/sqrt(fan_in), 1/sqrt(fan_in)) for weights and biases
     std::vector<float> h(np);
@@ -452,11 +689,10 @@ lb_status mlp_init(mlp_net** out, int seed, void* hip_stream) {
     }
     if (hipMemcpy(n->P, h.data(), sizeof(float) * np, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemset(n->G, 0, sizeof(float) * np) != hipSuccess || hipMemset(n->Mo, 0, sizeof(float) * np) != hipSuccess ||
-        hipMemset(n->Vo, 0, sizeof(float) * np) != hipSuccess)
+        hipMemset(n->Vo, 0, sizeof(float) * np) != hipSuccess ||
+        hipMemset(n->packed, 0, sizeof(float) * PACKED) != hipSuccess || hipDeviceSynchronize() != hipSuccess)
         return bail(lbk::set_error(LB_EDEVICE, "network initialisation failed"));
-    // set-up of the allocation-free inference path on this device
-    float* sc = nullptr;
-    if (lb_status st = noalloc_scratch(n->device, &sc)) return bail(st);
+    if (lb_status st = pack(n)) return bail(st);
     *out = n;
     return LB_OK;
 }
@@ -466,6 +702,9 @@ void mlp_free(mlp_net* n) {
     if (n->stream) (void)hipStreamSynchronize(n->stream);
     else (void)hipDeviceSynchronize();
     free_rows(n);
+    free_groups(n);
+    (void)hipFree(n->packed);
+    (void)hipFree(n->xcopy);
     (void)hipFree(n->P);
     (void)hipFree(n->G);
     (void)hipFree(n->Mo);
@@ -493,6 +732,7 @@ lb_status mlp_set_params(mlp_net* n, const float* host, long count) {
     MLP_TRY(hipMemcpyAsync(n->P, host, sizeof(float) * count, hipMemcpyHostToDevice, n->stream));
     MLP_TRY(hipMemsetAsync(n->Mo, 0, sizeof(float) * count, n->stream));
     MLP_TRY(hipMemsetAsync(n->Vo, 0, sizeof(float) * count, n->stream));
+    if (lb_status st = pack(n)) return st;
     MLP_TRY(hipStreamSynchronize(n->stream));
     n->adam_t = 0;
     return LB_OK;
@@ -503,10 +743,9 @@ lb_status mlp_predict(mlp_net* n, const float* X, int rows, float* Y) {
     if (rows < 0 || (rows > 0 && (!X || !Y))) return lbk::set_error(LB_EINVAL, "bad rows or null arrays");
     if (rows == 0) return LB_OK;
     if (lb_status st = ensure_rows(n, rows)) return st;
-    MLP_TRY(hipMemcpyAsync(n->act[0], X, sizeof(float) * (size_t)rows * DIMS[0], hipMemcpyHostToDevice, n->stream));
-    if (lb_status st = forward(n, rows)) return st;
-    MLP_TRY(hipMemcpyAsync(Y, n->z[NLAYER - 1], sizeof(float) * (size_t)rows * DIMS[NLAYER], hipMemcpyDeviceToHost,
-                           n->stream));
+    MLP_TRY(hipMemcpyAsync(n->x, X, sizeof(float) * (size_t)rows * DIMS[0], hipMemcpyHostToDevice, n->stream));
+    if (lb_status st = forward(n, n->x, rows, n->y)) return st;
+    MLP_TRY(hipMemcpyAsync(Y, n->y, sizeof(float) * (size_t)rows * DIMS[NLAYER], hipMemcpyDeviceToHost, n->stream));
     MLP_TRY(hipStreamSynchronize(n->stream));
     return LB_OK;
 }
@@ -517,28 +756,25 @@ lb_status mlp_predict_device_noalloc(mlp_net* n, const float* dX, int rows, floa
         return lbk::set_error(LB_EINVAL, "mlp_predict_device_noalloc: rows must be in 0..MLP_NOALLOC_MAX_ROWS (1024)");
     if (rows > 0 && (!dX || !dY)) return lbk::set_error(LB_EINVAL, "null device arrays");
     if (rows == 0) return LB_OK;
-    float* sc = nullptr;
-    if (lb_status st = noalloc_scratch(n->device, &sc)) return st;
-    // layer inputs: X, then the hidden activations alternating between the
-    // second and third scratch buffers; pre-activations of the hidden layers
-    // into the first (not read), the output straight into Y
-    float* const a = sc + SCRATCH_BUF;
-    float* const b = sc + 2 * SCRATCH_BUF;
-    const float* const in[NLAYER] = {dX, a, b, a};
-    float* const z[NLAYER] = {sc, sc, sc, dY};
-    return forward_bufs(n->stream, n->P, rows, in, z);
+    // rows are finished in any order: an output that overlaps the inputs needs a copy of them
+    const uintptr_t x0 = (uintptr_t)dX, x1 = x0 + sizeof(float) * (size_t)rows * DIMS[0];
+    const uintptr_t y0 = (uintptr_t)dY, y1 = y0 + sizeof(float) * (size_t)rows * DIMS[NLAYER];
+    if (x0 < y1 && y0 < x1) {
+        MLP_TRY(hipMemcpyAsync(n->xcopy, dX, x1 - x0, hipMemcpyDeviceToDevice, n->stream));
+        dX = n->xcopy;
+    }
+    return forward(n, dX, rows, dY);
 }
 
 lb_status mlp_loss_grad(mlp_net* n, const float* X, const float* Y, int rows, float* loss, float* grads) {
     if (lb_status st = check_net(n)) return st;
     if (rows <= 0 || !X || !Y) return lbk::set_error(LB_EINVAL, "bad rows or null arrays");
     if (lb_status st = ensure_rows(n, rows)) return st;
+    if (lb_status st = ensure_groups(n, rows)) return st;
     if (lb_status st = ensure_loss(n, 1)) return st;
-    MLP_TRY(hipMemcpyAsync(n->act[0], X, sizeof(float) * (size_t)rows * DIMS[0], hipMemcpyHostToDevice, n->stream));
-    MLP_TRY(hipMemcpyAsync(n->yb, Y, sizeof(float) * (size_t)rows * DIMS[NLAYER], hipMemcpyHostToDevice, n->stream));
-    if (lb_status st = forward(n, rows)) return st;
-    if (lb_status st = mse(n, rows, n->loss)) return st;
-    if (lb_status st = backward(n, rows)) return st;
+    MLP_TRY(hipMemcpyAsync(n->x, X, sizeof(float) * (size_t)rows * DIMS[0], hipMemcpyHostToDevice, n->stream));
+    MLP_TRY(hipMemcpyAsync(n->y, Y, sizeof(float) * (size_t)rows * DIMS[NLAYER], hipMemcpyHostToDevice, n->stream));
+    if (lb_status st = gradient(n, n->x, n->y, nullptr, rows, n->loss, false, 0.f)) return st;
     float l = 0.f;
     MLP_TRY(hipMemcpyAsync(&l, n->loss, sizeof(float), hipMemcpyDeviceToHost, n->stream));
     if (grads)
@@ -555,7 +791,7 @@ lb_status mlp_train(mlp_net* n, const float* X, const float* Y, int rows, int ep
         return lbk::set_error(LB_EINVAL, "bad training arguments");
     const int nb = (rows + batch - 1) / batch;   // minibatches per epoch, the last one may be short
     const int bmax = std::min(batch, rows);
-    if (lb_status st = ensure_rows(n, bmax)) return st;
+    if (lb_status st = ensure_groups(n, bmax)) return st;
     if (lb_status st = ensure_loss(n, nb)) return st;
     if (rows > n->data_cap) {
         MLP_TRY(hipStreamSynchronize(n->stream));
@@ -572,8 +808,6 @@ lb_status mlp_train(mlp_net* n, const float* X, const float* Y, int rows, int ep
     }
     MLP_TRY(hipMemcpyAsync(n->Xall, X, sizeof(float) * (size_t)rows * DIMS[0], hipMemcpyHostToDevice, n->stream));
     MLP_TRY(hipMemcpyAsync(n->Yall, Y, sizeof(float) * (size_t)rows * DIMS[NLAYER], hipMemcpyHostToDevice, n->stream));
-    const long np = param_count();
-    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
     std::vector<int> perm(rows);
     for (int e = 0; e < epochs; ++e) {
         // seeded Fisher-Yates shuffle of the rows
@@ -586,18 +820,7 @@ lb_status mlp_train(mlp_net* n, const float* X, const float* Y, int rows, int ep
         MLP_TRY(hipMemcpy(n->idx, perm.data(), sizeof(int) * (size_t)rows, hipMemcpyHostToDevice));
         for (int b = 0; b < nb; ++b) {
             const int r0 = b * batch, nr = std::min(batch, rows - r0);
-            hipLaunchKernelGGL(mlp_gather, dim3(nr), dim3(64), 0, n->stream, n->Xall, n->Yall, n->idx + r0, nr,
-                               DIMS[0], DIMS[NLAYER], n->act[0], n->yb);
-            MLP_TRY(hipGetLastError());
-            if (lb_status st = forward(n, nr)) return st;
-            if (lb_status st = mse(n, nr, n->loss + b)) return st;
-            if (lb_status st = backward(n, nr)) return st;
-            n->adam_t += 1;
-            const float bc1 = 1.f - (float)std::pow(0.9, (double)n->adam_t);
-            const float bc2 = 1.f - (float)std::pow(0.999, (double)n->adam_t);
-            hipLaunchKernelGGL(mlp_adam, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, n->stream, n->P, n->G,
-                               n->Mo, n->Vo, np, lr, b1, b2, eps, bc1, bc2);
-            MLP_TRY(hipGetLastError());
+            if (lb_status st = gradient(n, n->Xall, n->Yall, n->idx + r0, nr, n->loss + b, true, lr)) return st;
         }
     }
     if (last_loss) {
