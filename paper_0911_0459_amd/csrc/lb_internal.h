@@ -11,6 +11,16 @@ namespace lbk {
 // Records the message returned by lb_last_error and returns s.
 lb_status set_error(lb_status s, const char* msg);
 
+// Pinned host memory that the kernels of read-outs write (and mlp_predict's reads)
+// themselves, PIN_BYTES a piece.  An object takes a piece with its first read-out and
+// gives it back when it is freed, with its stream drained; up to PIN_KEPT pieces wait
+// for the next object (allocating one takes about 130 us), more are freed.
+// pin_take returns null if the allocation fails.
+constexpr size_t PIN_BYTES = 1 << 20;
+constexpr size_t PIN_KEPT = 4;
+char* pin_take();
+void pin_give(char* p);
+
 constexpr int TILE_W = 64;  // tile width along x = one wavefront
 
 // Per-capillary descriptor, resident in device memory.  Offsets are in floats

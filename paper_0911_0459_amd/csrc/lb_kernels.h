@@ -645,15 +645,15 @@ __global__ void __launch_bounds__(TILE_W* TY) lb_step_kernel(StepArgs a) {
 
 // ---- macroscopic fields of one capillary -----------------------------------
 // rho = rho_ref + sum s*, u = (j* - F/2)/rho (the collision added F to j), phi(t)
-// from the phi plane of the other arena.
+// from the phi plane of the other arena.  Nodes k0 .. k1-1, written from the start
+// of each array.
 template <int MODEL>
 __global__ void lb_moments_kernel(const CapDev* caps, int cap, const float* __restrict__ st,
-                                  const float* __restrict__ prev, float* rho_o, float* ux_o, float* uy_o,
-                                  float* phi_o) {
+                                  const float* __restrict__ prev, long long k0, long long k1, float* rho_o,
+                                  float* ux_o, float* uy_o, float* phi_o) {
     const CapDev& c = caps[cap];
     const Geo g = geo_of(c);
-    const long long n = (long long)g.nx * g.ny;
-    for (long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x; k < n;
+    for (long long k = k0 + blockIdx.x * (long long)blockDim.x + threadIdx.x; k < k1;
          k += (long long)gridDim.x * blockDim.x) {
         const int y = (int)(k / g.nx), x = (int)(k % g.nx);
         float r = 0.f, u = 0.f, v = 0.f, p = 0.f;
@@ -678,10 +678,10 @@ __global__ void lb_moments_kernel(const CapDev* caps, int cap, const float* __re
             v = jy / r;
             if (MODEL == 1) p = phi_of_fixed(prev[c.off_phi + own]);
         }
-        if (rho_o) rho_o[k] = r;
-        if (ux_o) ux_o[k] = u;
-        if (uy_o) uy_o[k] = v;
-        if (phi_o) phi_o[k] = p;
+        if (rho_o) rho_o[k - k0] = r;
+        if (ux_o) ux_o[k - k0] = u;
+        if (uy_o) uy_o[k - k0] = v;
+        if (phi_o) phi_o[k - k0] = p;
     }
 }
 
@@ -753,6 +753,19 @@ lb_interface_kernel(const CapDev* caps, int ncap, float* arena0, float* arena1, 
             }
             hist_n[cap] = n + 1;
         }
+    }
+}
+
+// ---- one capillary's history for the host -------------------------------------------
+// The number of samples and the first `most` of them into host memory.
+__global__ void __launch_bounds__(256)
+lb_history_kernel(const int* __restrict__ n, const float* __restrict__ l, const long long* __restrict__ t, int most,
+                  int* n_o, float* l_o, long long* t_o) {
+    const int have = *n;
+    if (threadIdx.x == 0) *n_o = have;
+    for (int i = threadIdx.x; i < min(have, most); i += 256) {
+        l_o[i] = l[i];
+        t_o[i] = t[i];
     }
 }
 

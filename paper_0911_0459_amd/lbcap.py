@@ -311,7 +311,7 @@ class Lattice:
     # -- observables -----------------------------------------------------------
     def moments(self, cap: int = 0):
         g = self.geoms[cap]
-        out = [np.zeros(g.nx * g.ny) for _ in range(4)]
+        out = [np.empty(g.nx * g.ny) for _ in range(4)]   # (written whole)
         _check(_lib.lb_batch_moments(self._h, cap, *[_d(o) for o in out]))
         return tuple(o.reshape(g.ny, g.nx) for o in out)
 
@@ -325,8 +325,8 @@ class Lattice:
         return l.value, le.value
 
     def l_history(self, cap: int = 0):
-        buf = np.zeros(LB_HISTORY_CAP)
-        steps = np.zeros(LB_HISTORY_CAP, dtype=np.int64)
+        buf = np.empty(LB_HISTORY_CAP)
+        steps = np.empty(LB_HISTORY_CAP, dtype=np.int64)
         n = C.c_int()
         _check(_lib.lb_batch_l_history(self._h, cap, _d(buf), steps.ctypes.data_as(_lp), LB_HISTORY_CAP,
                                        C.byref(n)))
@@ -429,7 +429,7 @@ class MLP:
 
     def predict(self, X: np.ndarray) -> np.ndarray:
         X = np.ascontiguousarray(X, dtype=np.float32)
-        Y = np.zeros((X.shape[0], self.N_OUT), dtype=np.float32)
+        Y = np.empty((X.shape[0], self.N_OUT), dtype=np.float32)
         _check(_lib.mlp_predict(self._h, _f32(X), X.shape[0], _f32(Y)))
         return Y
 

@@ -73,3 +73,24 @@ def test_binary_tiles_do_not_depend_on_the_grouping(L, name, fp64, force):
             assert np.array_equal(x, y)
     pop = _run(L, "binary", g, dict(schedule=4, fp64_arith=fp64), [13], force)
     assert max(float(np.abs(x - y).max()) for x, y in zip(ref, pop)) <= 2e-6
+
+
+def test_fields_through_several_pinned_chunks(L):
+    """Host fields pass through pinned memory half a buffer (32768 nodes) at a time: a
+    lattice of three halves and a bit reads the same as on the device."""
+    import torch
+    g = (700, 153, 100, 400, 90, 30)
+    rng = np.random.default_rng(3)
+    q = np.where(np.arange(g[0]) < 300, 1.0, -1.0) + 1e-3 * rng.uniform(-1, 1, (g[1], g[0]))
+    lat = L.Lattice(L.make_params("binary", nu_l=0.4, nu_g=0.1, wall_grad=-0.2, **I.BIN_CONSTS), L.make_geometry(*g), q)
+    lat.step(30)
+    dev = [torch.full((g[1], g[0]), float("nan"), device="cuda") for _ in range(4)]
+    lat.moments_device(*dev)
+    host = lat.moments()
+    torch.cuda.synchronize()
+    for x, y in zip(host, dev):
+        assert np.array_equal(x, y.cpu().numpy().astype(np.float64))
+    lat.step(1)
+    again = lat.moments()
+    assert all(np.all(np.isfinite(x)) for x in again) and not np.array_equal(again[1], host[1])
+    lat.close()
