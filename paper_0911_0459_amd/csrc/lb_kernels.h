@@ -297,7 +297,9 @@ __device__ __forceinline__ void pops_of_state(const PostState<R>& s, R (&o)[9]) 
 // LAM = false drops the Galilean terms at compile time (lam must then be 0, as
 // in the binary model) and FORCE = false the forcing terms (F must then be 0);
 // the results are the same, with fewer instructions.
-template <typename R, typename S = R, bool LAM = true, bool FORCE = true>
+// PIN (FP32) spells out the FMAs of b and d, which the compiler would choose by the
+// code around.
+template <typename R, typename S = R, bool LAM = true, bool FORCE = true, bool PIN = false>
 __device__ __forceinline__ PostState<R> collide_state(const CapDev& c, const Mom<R>& m, R rho, R ux, R uy, R dX,
                                                       R lam, R lam_b, R omega, R dxq, R dyq, R F) {
     const R kappa = (R)c.kappa;
@@ -314,10 +316,16 @@ __device__ __forceinline__ PostState<R> collide_state(const CapDev& c, const Mom
     const R uF = ux * F;
     // common parts of the axis (b) and diagonal (d) populations minus their
     // reference values X_ref/3 and X_ref/12 (e, eps at equilibrium plus source)
-    const R b = FORCE ? dX * (R(1) / R(3)) + (trQ + kappa * grad2 + uF) * (R(1) / R(12))
-                      : dX * (R(1) / R(3)) + (trQ + kappa * grad2) * (R(1) / R(12));
-    const R d = FORCE ? dX * (R(1) / R(12)) + (trQ - R(0.5) * kappa * grad2 + uF) * (R(1) / R(12))
-                      : dX * (R(1) / R(12)) + (trQ - R(0.5) * kappa * grad2) * (R(1) / R(12));
+    const R pb = FORCE ? trQ + kappa * grad2 + uF : trQ + kappa * grad2;
+    const R pd = FORCE ? trQ - R(0.5) * kappa * grad2 + uF : trQ - R(0.5) * kappa * grad2;
+    R b, d;
+    if constexpr (PIN) {
+        b = __builtin_fmaf(pb, R(1) / R(12), dX * (R(1) / R(3)));
+        d = __builtin_fmaf(pd, R(1) / R(12), dX * (R(1) / R(12)));
+    } else {
+        b = dX * (R(1) / R(3)) + pb * (R(1) / R(12));
+        d = dX * (R(1) / R(12)) + pd * (R(1) / R(12));
+    }
     const R hw = R(1) - R(0.5) * omega;
     const R pxr = (R)((S)m.pxx - (S)omega * ((S)m.pxx - pxx_eq));
     const R pyr = (R)((S)m.pxy - (S)omega * ((S)m.pxy - pxy_eq));

@@ -41,28 +41,30 @@ struct StripArgs {
 };
 
 // Stencils of Eq. (best) on three LDS rows (below, centre, above) at index j,
-// wall ghosts as in `stencil`.
+// wall ghosts as in `stencil`.  The ghosts are picked among the nine values already
+// read: reads under a branch per direction would each wait for LDS, and the other
+// wavefronts of a workgroup wait for the one at the wall.
 __device__ __forceinline__ void stencil3(const float* __restrict__ rm, const float* __restrict__ r0,
                                          const float* __restrict__ rp, int j, unsigned sm, float G2, float& dxq,
                                          float& dyq, float& lapq) {
-    auto Q = [&](int dx, int dy) -> float { return (dy < 0 ? rm : (dy > 0 ? rp : r0))[j + dx]; };
     const float qc = r0[j];
-    float v1 = Q(1, 0) - qc, v2 = Q(-1, 0) - qc, v3 = Q(0, 1) - qc, v4 = Q(0, -1) - qc;
-    float v5 = Q(1, 1) - qc, v6 = Q(-1, -1) - qc, v7 = Q(-1, 1) - qc, v8 = Q(1, -1) - qc;
+    const float a1 = r0[j + 1] - qc, a2 = r0[j - 1] - qc, a3 = rp[j] - qc, a4 = rm[j] - qc;
+    const float a5 = rp[j + 1] - qc, a6 = rm[j - 1] - qc, a7 = rp[j - 1] - qc, a8 = rm[j + 1] - qc;
+    float v1 = a1, v2 = a2, v3 = a3, v4 = a4, v5 = a5, v6 = a6, v7 = a7, v8 = a8;
     if (sm) {
-        if (sm & (1u << 1)) v1 = (Q(-1, 0) - qc) - G2;
-        if (sm & (1u << 2)) v2 = (Q(1, 0) - qc) - G2;
-        if (sm & (1u << 3)) v3 = (Q(0, -1) - qc) - G2;
-        if (sm & (1u << 4)) v4 = (Q(0, 1) - qc) - G2;
-        auto diag = [&](int dx, int dy, int dxi, int dyi) -> float {
-            if (sm & (1u << dxi)) return (Q(-dx, dy) - qc) - G2;
-            if (sm & (1u << dyi)) return (Q(dx, -dy) - qc) - G2;
-            return (Q(-dx, -dy) - qc) - G2;
+        auto solid = [&](int d) { return ((sm >> d) & 1u) != 0u; };
+        // a diagonal neighbour: mirrored in x, in y or through the node
+        auto diag = [&](int dxi, int dyi, float mx, float my, float mxy) {
+            return (solid(dxi) ? mx : (solid(dyi) ? my : mxy)) - G2;
         };
-        if (sm & (1u << 5)) v5 = diag(1, 1, 1, 3);
-        if (sm & (1u << 6)) v6 = diag(-1, -1, 2, 4);
-        if (sm & (1u << 7)) v7 = diag(-1, 1, 2, 3);
-        if (sm & (1u << 8)) v8 = diag(1, -1, 1, 4);
+        v1 = solid(1) ? a2 - G2 : a1;
+        v2 = solid(2) ? a1 - G2 : a2;
+        v3 = solid(3) ? a4 - G2 : a3;
+        v4 = solid(4) ? a3 - G2 : a4;
+        v5 = solid(5) ? diag(1, 3, a7, a8, a6) : a5;
+        v6 = solid(6) ? diag(2, 4, a8, a7, a5) : a6;
+        v7 = solid(7) ? diag(2, 3, a5, a6, a8) : a7;
+        v8 = solid(8) ? diag(1, 4, a6, a5, a7) : a8;
     }
     dxq = ((v5 + v8) - (v7 + v6) + 4.f * (v1 - v2)) * (1.f / 12.f);
     dyq = ((v5 + v7) - (v8 + v6) + 4.f * (v3 - v4)) * (1.f / 12.f);
@@ -198,7 +200,10 @@ __device__ __forceinline__ float recip(float x) {
 // once, before the loop, and held in a pair of vector registers for the whole
 // sweep; vector registers bound the occupancy of these kernels, the
 // conversions are cheap.
-__device__ __forceinline__ void uniform_opaque(float& v) { asm volatile("" : "+s"(v)); }
+template <typename CT>
+__device__ __forceinline__ void uniform_opaque(float& v) {
+    if constexpr (sizeof(CT) == 8) asm volatile("" : "+s"(v));
+}
 
 // Pull of the lane's node on a row (bounce-back for solid sources).  Straight-line
 // code, the source chosen by selects: a branch around the loads (even a uniform
@@ -258,7 +263,7 @@ __device__ __forceinline__ float phi_delta(unsigned sm, float phi, float ux, flo
         return (a - am) + adv(i, p, x, y);
     };
     float sa = 0.f, sd = 0.f;   // axis and diagonal sums
-    if (sm == 0u) {   // no solid neighbour: every source streams
+    if (__builtin_amdgcn_ballot_w64(sm != 0u) == 0) {   // no solid neighbours: every source streams
 #pragma unroll
         for (int i = 1; i < 9; ++i) {
             if (i <= 4) sa += incoming(i);
@@ -267,7 +272,8 @@ __device__ __forceinline__ float phi_delta(unsigned sm, float phi, float ux, flo
     } else {
 #pragma unroll
         for (int i = 1; i < 9; ++i) {
-            const float t = ((sm >> opp_(i)) & 1u) ? adv(opp_(i), phi, ux, uy) : incoming(i);
+            const float in = incoming(i), back = adv(opp_(i), phi, ux, uy);
+            const float t = ((sm >> opp_(i)) & 1u) ? back : in;
             if (i <= 4) sa += t;
             else sd += t;
         }
@@ -499,14 +505,14 @@ __device__ __forceinline__ void vdw_node_collide(const CapDev& c, const Mom<floa
                                                  float dyf, float lapf, CT (&o)[9]) {
     // constants of the FP64 part, converted where used (see uniform_opaque)
     CapDev cd = c;
-    uniform_opaque(cd.Fx);
-    uniform_opaque(cd.rho_ref);
-    uniform_opaque(cd.T);
-    uniform_opaque(cd.a);
-    uniform_opaque(cd.b);
-    uniform_opaque(cd.ibr);
-    uniform_opaque(cd.kappa);
-    uniform_opaque(cd.omega_l);
+    uniform_opaque<CT>(cd.Fx);
+    uniform_opaque<CT>(cd.rho_ref);
+    uniform_opaque<CT>(cd.T);
+    uniform_opaque<CT>(cd.a);
+    uniform_opaque<CT>(cd.b);
+    uniform_opaque<CT>(cd.ibr);
+    uniform_opaque<CT>(cd.kappa);
+    uniform_opaque<CT>(cd.omega_l);
     const bool bnd = sm != 0u;
     const CT F = (FORCE && !bnd) ? (CT)cd.Fx : CT(0);
     const Mom<CT> m{(CT)mom.drho, (CT)mom.jx, (CT)mom.jy, (CT)mom.pxx, (CT)mom.pxy};
@@ -538,11 +544,11 @@ __device__ __forceinline__ PostState<CT> bin_node_state(const CapDev& c, const M
                                                         float uyf) {
     // constants of the FP64 part, converted where used (see uniform_opaque)
     CapDev cd = c;
-    uniform_opaque(cd.kappa);
-    uniform_opaque(cd.Fx);
-    uniform_opaque(cd.rho_ref);
-    uniform_opaque(cd.phib);
-    uniform_opaque(cd.B);
+    uniform_opaque<CT>(cd.kappa);
+    uniform_opaque<CT>(cd.Fx);
+    uniform_opaque<CT>(cd.rho_ref);
+    uniform_opaque<CT>(cd.phib);
+    uniform_opaque<CT>(cd.B);
     const Mom<CT> mc{(CT)mom.drho, (CT)mom.jx, (CT)mom.jy, (CT)mom.pxx, (CT)mom.pxy};
     const CT F = (FORCE && !sm) ? (CT)cd.Fx : CT(0);
     const CT rho = (CT)cd.rho_ref + mc.drho;
@@ -556,15 +562,18 @@ __device__ __forceinline__ PostState<CT> bin_node_state(const CapDev& c, const M
         uy = mc.jy * inv_rho;
     }
     const CT ph = (CT)phi, phib = (CT)cd.phib;
-    const CT dX = mc.drho * (CT(1) / CT(3)) +
-                  CT(0.25) * (CT)cd.B * ((ph - phib) * (ph + phib)) * (CT(3) * ph * ph + phib * phib) -
-                  (CT)cd.kappa * ph * (CT)lapf;
+    const CT bulk = CT(0.25) * (CT)cd.B * ((ph - phib) * (ph + phib)) * (CT(3) * ph * ph + phib * phib);
+    CT dX;
+    if constexpr (sizeof(CT) == 4)   // the FMAs spelled out: the compiler's choice depends on the code around
+        dX = __builtin_fmaf(-(cd.kappa * ph), lapf, __builtin_fmaf(mc.drho, 1.f / 3.f, bulk));
+    else
+        dX = mc.drho * (CT(1) / CT(3)) + bulk - (CT)cd.kappa * ph * (CT)lapf;
     // the relaxation rate only scales the shear stresses (FP32) and the
     // forcing term: FP32 with the hardware reciprocal (1 ulp)
     const float pc = phi < -1.f ? -1.f : (phi > 1.f ? 1.f : phi);
     const float nu = cd.nu_g + 0.5f * (pc + 1.f) * (cd.nu_l - cd.nu_g);
     const CT omega = (CT)(2.f * __builtin_amdgcn_rcpf(6.f * nu + 1.f));
-    return collide_state<CT, ST, false, FORCE>(cd, mc, rho, ux, uy, dX, CT(0), CT(0), omega, (CT)dxf, (CT)dyf, F);
+    return collide_state<CT, ST, false, FORCE, sizeof(CT) == 4>(cd, mc, rho, ux, uy, dX, CT(0), CT(0), omega, (CT)dxf, (CT)dyf, F);
 }
 
 template <typename CT, bool FORCE = true>
