@@ -455,6 +455,8 @@ template <int MODEL, typename CT>
 void launch_block_s(lb_ctx* c, const BlockArgs& a, int grid) {
     if (c->block_shape == 0)
         launch_block_f<BlockShape<32, 32, 32>, MODEL, CT>(c, a, grid);
+    else if (c->block_shape == 2)
+        launch_block_f<BlockShape<32, 24, 24>, MODEL, CT>(c, a, grid);
     else if constexpr (MODEL == 0)
         launch_block_f<BlockShape<64, 32, 16>, MODEL, CT>(c, a, grid);
     else

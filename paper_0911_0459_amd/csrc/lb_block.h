@@ -25,7 +25,7 @@
 // and two barriers (1.1 us a step for van der Waals, 1.8 us for the binary model)
 // and a K-th of 3.5 us for the launch, the loads and the stores.  The row sweeps,
 // marching a few dozen workgroups through their rows at about 2 us a row, left most
-// CUs idle: vdW 256 x 64 10.1 -> 1.7 us per step, binary 1024 x 128 46.2 -> 2.7 us,
+// CUs idle: vdW 256 x 64 10.1 -> 1.6 us per step, binary 1024 x 128 46.2 -> 2.7 us,
 // binary 4096 x 256 47.1 -> 8.9 us.  A large one is bound by the vector ALU (vdW
 // 16384 x 1024 at K = 4: 45 M wavefront instructions a step, all its cycles; the
 // 256-capillary sweep: 80 % of them; halo nodes are a third to a half of the work):

@@ -79,43 +79,48 @@ inline size_t build_blocks(const std::vector<lb_geometry>& G, const std::vector<
 
 // How a context's lattices are cut: a shape (0: 32 x 32 nodes, one node per
 // thread; 1: 64 columns, two nodes per thread, 24 rows for the binary model, 32
-// for van der Waals: what two workgroups per CU leave in LDS) and K.
+// for van der Waals: what two workgroups per CU leave in LDS; 2: 32 x 24 nodes) and K.
 struct BlockPlan {
     int shape, K;
     size_t tiles;
 };
 
-constexpr int BLOCK_SHAPES = 2;
-inline int block_rx(int shape) { return shape == 0 ? 32 : 64; }
-inline int block_ry(int shape, bool vdw) { return shape == 0 || vdw ? 32 : 24; }
+constexpr int BLOCK_SHAPES = 3;
+inline int block_rx(int shape) { return shape == 1 ? 64 : 32; }
+inline int block_ry(int shape, bool vdw) { return shape == 2 || (shape == 1 && !vdw) ? 24 : 32; }
 // Columns the tiles are cut at.  A lattice beyond the caches is bound by the lines
 // its tiles share: whole 64-byte sectors measured 71.9 against 74.0 us per step
 // (vdW 16384 x 1024, K = 4).  The binary tiles (K = 2: 56 columns) would lose more
 // columns than that gains (the 256-capillary sweep: 422 against 374 us).
 inline int block_align(int shape, bool vdw) { return shape == 1 && vdw ? 16 : 1; }
 
-// The cheapest plan.  A launch costs its own latency, which grows with K, and, once
-// every CU has a tile, so much for every further tile per CU.  Both are linear
-// fits (us) to lattices of 1e4 to 3e7 nodes; they hold to 10 - 20 %, which is
-// less than the candidates differ where it matters: small shape and large K while
-// the CUs are idle (binary 256 x 64: 2.6 us a step at K = 6, 3.8 at K = 2), small K
-// when halos cost throughput (binary 4096 x 256: 8.7 us at K = 2, 12.1 at K = 4), the
-// large shape, with fewer halo nodes, from about a million nodes (the
-// 256-capillary sweep: 374 us against 440).
+// The cheapest plan.  A launch costs its own latency, which grows with K, and so much
+// for every further tile of a CU: whole rounds of 256 tiles up to the second (the 5 x
+// 512 x 64 batch of the binary model: 250 tiles at K = 3 3.05 us a step, 290 at K = 4
+// 3.63), a continuous flow of tiles beyond.  The coefficients are fits (us) to
+// lattices of 5e3 to 7e6 nodes; they hold to 6 - 8 % (rms), and the plan they choose
+// was the best of the 11 or 12 measured ones on 27 of 30 lattices (2 %, 7 % and 15 %
+// off on the others).  The 24-row shape has fewer wavefronts to take through each step
+// while CUs are idle (binary 131 x 41 1.97 us a step against 2.08, 256 x 64 1.97
+// against 2.06); a small K when halos cost throughput (binary 4096 x 256: 8.2 us at
+// K = 2, 10.6 at K = 4), the large shape, with fewer halo nodes, from about a million
+// nodes (binary 8192 x 1024: 79 against 102 us).
 inline BlockPlan plan_block_tiles(const std::vector<lb_geometry>& G, const std::vector<int>& active, bool vdw) {
     struct Cost {
         int shape, kmin, kmax;
         double launch, launch_k, tile, tile_k;
     };
-    static const Cost binary[] = {{0, 2, 6, 3.6, 2.1, 1.9, 0.65}, {1, 2, 3, 6.5, 2.4, 3.6, 0.5}};
-    static const Cost van[] = {{0, 2, 6, 3.2, 1.22, 2.4, 0.22}, {1, 2, 4, 3.7, 2.1, 5.9, 0.0}};
+    static const Cost binary[] = {
+        {0, 2, 6, 2.8, 1.64, 2.57, 0.44}, {1, 2, 3, 4.4, 2.07, 3.95, 0.46}, {2, 2, 5, 2.5, 1.47, 2.02, 0.30}};
+    static const Cost van[] = {
+        {0, 2, 6, 2.84, 1.10, 2.85, 0.06}, {1, 2, 4, 3.64, 1.83, 4.79, 0.23}, {2, 2, 5, 2.66, 0.99, 2.09, 0.05}};
     BlockPlan best{0, 0, 0};
     double cheapest = 0.0;
     for (const Cost& c : vdw ? van : binary)
         for (int K = c.kmin; K <= c.kmax; ++K) {
             const size_t n = build_blocks(G, active, K, block_rx(c.shape), block_ry(c.shape, vdw),
                                           block_align(c.shape, vdw), nullptr);
-            const double over = n > 256 ? n / 256.0 - 1.0 : 0.0;
+            const double over = n <= 512 ? (n > 256 ? 1.0 : 0.0) : n / 256.0 - 0.5;
             const double us = (c.launch + c.launch_k * K + (c.tile + c.tile_k * K) * over) / K;
             if (best.K == 0 || us < cheapest) {
                 best = BlockPlan{c.shape, K, n};
