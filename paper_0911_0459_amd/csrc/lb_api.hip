@@ -818,8 +818,8 @@ lb_status create(lb_ctx** out, int n, const lb_params* P, const lb_geometry* G, 
         hipMemsetAsync(c->d_flags, 0, sizeof(int) * n, c->stream) != hipSuccess ||
         hipMemsetAsync(c->d_lnow, 0, sizeof(float) * n, c->stream) != hipSuccess)
         return bail(fail(LB_EDEVICE, "upload of descriptors failed"));
-    // default launch shape: the moment storage for the binary model (its
-    // fastest sweep), the wide population sweep for van der Waals
+    // default launch shape: tiles of several steps; the moment storage for the binary
+    // model, the populations for van der Waals
     if (c->model == LB_BINARY) {
         c->cfg.schedule = 6;
         c->cfg.chunk_rows = 20;
