@@ -2,7 +2,7 @@
 // with GELU activations, trained by mean-squared error and Adam, all on the
 // device in FP32.
 //
-// Two kernels.  mlp_rows takes a few rows through all four layers (and, for the
+// Two kernels (and mlp_row, a forward pass of few rows).  mlp_rows takes a few rows through all four layers (and, for the
 // gradient, back again): the activations of the rows stay in LDS and registers,
 // the weights stream through once per direction.  mlp_wgrad forms every weight
 // and bias gradient from the activations and output gradients that mlp_rows left
@@ -315,6 +315,66 @@ __global__ void __launch_bounds__(256, GRAD && MT == 2 ? 2 : 1) mlp_rows(RowsArg
     }
 }
 
+// acc = sum over k of h[k] W(column of the lane, k), in the order of k: product P of the
+// stream for one row h in LDS, by vector FMAs.
+template <int P, int AHEAD>
+__device__ __forceinline__ float row_product(Stream<false, AHEAD>& s, const float* h) {
+    constexpr int NC = CHUNK0[P + 1] - CHUNK0[P];
+    float acc = 0.f;
+    f4 a[2][4];
+    auto read = [&](f4 (&to)[4], int c) {
+        int at = 16 * c;
+        asm volatile("" : "+v"(at));   // (or the reads of all chunks come first)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) to[q] = *(const f4*)&h[at + 4 * q];
+    };
+    read(a[0], 0);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        const int g = CHUNK0[P] + c;
+        s.request(g + AHEAD);
+        if (c + 1 < NC) read(a[(c + 1) & 1], c + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            acc = __builtin_fmaf(a[c & 1][k / 4][k % 4], s.w[g % (AHEAD + 1)][k / 4][k % 4], acc);
+        asm volatile("" : "+v"(acc));   // (or the sums come after all requests)
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    return acc;
+}
+
+// The forward pass with one row per workgroup, as long as every row has a CU.  The
+// matrix instruction takes four rows at a time, 16 cycles a link of the chain of
+// products; a vector FMA takes 4, with the same sums (one rounding per product, in the
+// order of k), and each lane has one activation to evaluate instead of four.  What is
+// left is the weights' way into the CU (0.6 MB at 64 bytes a cycle, 4 us).  One row
+// 8.3 -> 7.3 us a call, 256 rows 8.8 -> 8.0, 300 rows (two rounds) 8.8 -> 13.3; the
+// gradient pass gains nothing (256 rows 102 us either way).
+__global__ void __launch_bounds__(256, 1) mlp_row(RowsArgs a) {
+    __shared__ float H[2][WMAX];   // activations, two layers in turn
+    const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    // (the row before the weights, as in mlp_rows)
+    const float xv = t < DIMS[0] ? a.X[(long)blockIdx.x * DIMS[0] + t] : 0.f;
+    Stream<false, 7> ws;
+    ws.init(a.packed, wv, lane);
+    if (t < KPAD[0]) H[0][t] = xv;
+    lds_barrier();
+#pragma unroll
+    for (int l = 0; l < NLAYER - 1; ++l) {
+        const float bias = a.P[b_off(l) + t];
+        const float* h = H[l & 1];
+        const float z =
+            (l == 0 ? row_product<0>(ws, h) : l == 1 ? row_product<1>(ws, h) : row_product<2>(ws, h)) + bias;
+        H[(l & 1) ^ 1][t] = gelu(z, gelu_e1(z));
+        lds_barrier();
+    }
+    // the 64 outputs: every wavefront does the same work, the first one keeps the result
+    const float bias = a.P[b_off(NLAYER - 1) + lane];
+    const float o = row_product<3>(ws, H[(NLAYER - 1) & 1]) + bias;
+    if (wv == 0) a.out[(long)blockIdx.x * DIMS[NLAYER] + lane] = o;
+}
+
 // Adam (Kingma & Ba 2015, Algorithm 1); bc1 = 1 - beta1^t, bc2 = 1 - beta2^t.
 struct AdamArgs {
     float *P, *m, *v, *packed;
@@ -567,10 +627,10 @@ void launch_rows(const mlp_net* net, const RowsArgs& a, int work) {
     hipLaunchKernelGGL((mlp_rows<MT, GRAD>), dim3(work), dim3(256), 0, net->stream, a);
 }
 
-// Forward pass of n rows of X into out.  Rows per workgroup: 4 are the matrix
-// instruction's least and leave every product a single chain (10 us, of which 4 are
-// the launch's), 8 run two chains in the same time per workgroup, 16 share each
-// weight among most rows.  Measured, us, with 4 / 8 / 16 rows: 17.7 / 13.6 / 19.6 at
+// Forward pass of n rows of X into out.  One row per workgroup while there is a CU for
+// each (mlp_row).  Rows per workgroup beyond: 4 are the matrix instruction's least and
+// leave every product a single chain (10 us, of which 4 are the launch's), 8 run two
+// chains in the same time per workgroup, 16 share each weight among most rows.  Measured, us, with 4 / 8 / 16 rows: 17.7 / 13.6 / 19.6 at
 // 1100 rows, 19.4 / 14.4 / 19.3 at 2048, 35.2 / 23.4 / 21.2 at 4096, 128 / 80 / 66 at
 // 16384 (four products as launches of their own: 22 us each at 507 rows).
 lb_status forward(const mlp_net* net, const float* X, int n, float* out) {
@@ -580,7 +640,9 @@ lb_status forward(const mlp_net* net, const float* X, int n, float* out) {
     a.X = X;
     a.n = n;
     a.out = out;
-    if (n <= 1024)
+    if (n <= 256)
+        hipLaunchKernelGGL(mlp_row, dim3(n), dim3(256), 0, net->stream, a);
+    else if (n <= 1024)
         launch_rows<1, false>(net, a, (n + 3) / 4);
     else if (n <= 2048)
         launch_rows<2, false>(net, a, (n + 7) / 8);

@@ -1,4 +1,4 @@
-"""The network's kernels at the edges of their row tiles (4, 8 and 16 rows per
+"""The network's kernels at the edges of their row tiles (1, 4, 8 and 16 rows per
 workgroup, groups of 16 rows in the gradient), against the FP64 oracle at the
 tolerances of test_gpu_mlp.py, and the independence of the tiling: every product is a
 chain in the order of its terms, so a row's outputs do not depend on the rows it is
@@ -21,7 +21,7 @@ def L():
     return lbcap
 
 
-@pytest.mark.parametrize("n", [3, 4, 5, 1024, 1025, 2048, 2049, 2065])
+@pytest.mark.parametrize("n", [3, 4, 5, 256, 257, 1024, 1025, 2048, 2049, 2065])
 def test_forward_at_tile_edges(L, n):
     net = L.MLP(seed=31)
     X, _ = _data(n, seed=n)
