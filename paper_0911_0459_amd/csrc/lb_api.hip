@@ -357,7 +357,9 @@ struct lb_ctx {
 
 namespace {
 
+// (a replay may still be running: its graph lives until the stream has been waited for)
 void drop_graphs(lb_ctx* c) {
+    if (c->gexec[0] || c->gexec[1]) (void)hipStreamSynchronize(c->stream);
     for (int p = 0; p < 2; ++p) {
         if (c->gexec[p]) (void)hipGraphExecDestroy(c->gexec[p]);
         if (c->graph[p]) (void)hipGraphDestroy(c->graph[p]);

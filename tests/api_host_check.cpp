@@ -1,0 +1,73 @@
+// Checks of the library's host logic on a HIP runtime of host memory (host_hip.h):
+// the name of one check is the argument.
+#include <cstdio>
+
+#include "lb_api.hip"
+
+#include "host_hip.h"
+
+#define EXPECT(x)                                                     \
+    do {                                                              \
+        if (!(x)) {                                                   \
+            std::printf("%s:%d: %s\n", __FILE__, __LINE__, #x);     \
+            return 1;                                                 \
+        }                                                             \
+    } while (0)
+
+static lb_params params(lb_model m) {
+    lb_params p{};
+    p.model = m;
+    p.kappa = m == LB_VDW ? 0.02 : 0.04;
+    p.a = 9.0 / 49.0, p.b = 2.0 / 21.0, p.T = 0.56;
+    p.A = p.B = 0.04, p.Gamma = 1.0;
+    p.nu_l = p.nu_g = 0.2;
+    p.theta_deg = std::nan("");
+    p.q_mid = std::nan("");
+    return p;
+}
+
+// n capillaries of one model
+static lb_ctx* context(lb_model m, const std::vector<lb_geometry>& g) {
+    std::vector<lb_params> p(g.size(), params(m));
+    std::vector<std::vector<double>> q;
+    std::vector<const double*> qp;
+    for (const lb_geometry& x : g) q.emplace_back((size_t)x.nx * x.ny, m == LB_VDW ? 3.0 : 0.5);
+    for (const auto& x : q) qp.push_back(x.data());
+    lb_ctx* c = nullptr;
+    return lb_batch_init(&c, (int)g.size(), p.data(), g.data(), qp.data(), nullptr) == LB_OK ? c : nullptr;
+}
+
+static const lb_geometry SMALL{256, 64, 128, 128, 20, 22};
+
+// An executable graph is destroyed only after the stream has been waited for.
+static int graphs_outlive_their_replays() {
+    for (lb_model m : {LB_VDW, LB_BINARY}) {
+        lb_ctx* c = context(m, {SMALL, SMALL});
+        EXPECT(c);
+        EXPECT(lb_step(c, 200) == LB_OK && rt.replays > 0 && rt.pending);
+        EXPECT(lb_batch_retire(c, 1) == LB_OK);
+        EXPECT(rt.destroyed_pending == 0);
+        EXPECT(lb_step(c, 200) == LB_OK && rt.pending);
+        lb_launch_config cfg;
+        EXPECT(lb_get_launch_config(c, &cfg) == LB_OK);
+        cfg.graph_steps = 0;
+        EXPECT(lb_set_launch_config(c, &cfg) == LB_OK);
+        EXPECT(rt.destroyed_pending == 0);
+        lb_free(c);
+        EXPECT(rt.destroyed_pending == 0);
+    }
+    return 0;
+}
+
+int main(int argc, char** argv) {
+    const struct {
+        const char* name;
+        int (*run)();
+    } checks[] = {
+        {"graphs_outlive_their_replays", graphs_outlive_their_replays},
+    };
+    for (const auto& k : checks)
+        if (argc == 2 && std::string(argv[1]) == k.name) return k.run();
+    std::printf("no such check\n");
+    return 2;
+}
