@@ -121,7 +121,9 @@ lb_status lb_init(lb_ctx** out, const lb_params* p, const lb_geometry* g, const 
  * binary model): moments, stencils of Eq. (best), equilibria, MRT collision
  * with the rates of Appendix A, streaming with bounce-back, rest of boundary
  * nodes.  Asynchronous; errors of the launches are reported here, a numerical
- * blow-up by lb_check or the next call that reads data back. */
+ * blow-up by lb_check or the next call that reads data back.  LB_ESTATE if the
+ * last call that sets what is launched (a launch configuration, retire, revive,
+ * lb_load) failed on the device: repeating that call mends it. */
 lb_status lb_step(lb_ctx* c, long nsteps);
 
 /* Number of steps taken since lb_init / lb_load. */

@@ -351,6 +351,8 @@ struct lb_ctx {
     hipEvent_t pin_ev[2] = {nullptr, nullptr};   // a half of it is written
     long timed_steps = 0;
     int unstable = 0;
+    bool caps_stale = false;  // an upload of descriptors failed
+    bool tiled = false;       // the tables on the device are those of cfg and the active capillaries
     bool any_force = false;   // some capillary has a body force (row sweeps keep the forcing terms)
     int mstore = 0;           // 1: the arenas hold the seven-plane post-collision state (schedule 6)
 };
@@ -385,13 +387,19 @@ lb_status convert_arena(lb_ctx* c, int b, int to_state) {
     return LB_OK;
 }
 
+lb_status upload_caps(lb_ctx* c) {
+    c->caps_stale = true;
+    HIP_TRY(hipMemcpyAsync(c->d_caps, c->L.caps.data(), sizeof(CapDev) * c->n, hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    c->caps_stale = false;
+    return LB_OK;
+}
+
 // Records the storage the arenas hold (without converting them).
 lb_status mark_storage(lb_ctx* c, int m) {
     c->mstore = m;
     for (CapDev& d : c->L.caps) d.mstore = m;
-    HIP_TRY(hipMemcpyAsync(c->d_caps, c->L.caps.data(), sizeof(CapDev) * c->n, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    return LB_OK;
+    return upload_caps(c);
 }
 
 // Switches both arenas (all capillaries, retired ones too) to storage m.
@@ -491,8 +499,16 @@ void enqueue_block(lb_ctx* c, int steps) {
     }
 }
 
+// Nothing steps on tables that did not reach the device.
+lb_status check_tiled(const lb_ctx* c) {
+    return c->tiled ? LB_OK : fail(LB_ESTATE, "the last upload of the launch tables failed; repeat the call that set them");
+}
+
 lb_status upload_tiles(lb_ctx* c) {
     drop_graphs(c);
+    c->tiled = false;
+    if (c->caps_stale)
+        if (lb_status s = upload_caps(c)) return s;
     c->nstrips = c->nblocks = c->block_k = 0;
     std::vector<TileDev> tiles;
     build_tiles(c->G, c->active, c->cfg.tile_rows, tiles);
@@ -510,7 +526,10 @@ lb_status upload_tiles(lb_ctx* c) {
         HIP_TRY(hipMemcpyAsync(c->d_strips, strips.data(), sizeof(StripDev) * strips.size(), hipMemcpyHostToDevice,
                                c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
-    return uses_blocks(c) ? upload_blocks(c) : LB_OK;
+    if (uses_blocks(c))
+        if (lb_status s = upload_blocks(c)) return s;
+    c->tiled = true;
+    return LB_OK;
 }
 
 template <int MODEL, int TY, bool INIT, typename R>
@@ -677,6 +696,7 @@ bool graphs_used(const lb_ctx* c, long n) {
 // The graphs a run of n steps will replay, captured beforehand (so that the
 // capture is not inside a caller's timed region).
 lb_status prepare_graphs(lb_ctx* c, long n) {
+    if (lb_status s = check_tiled(c)) return s;
     if (!graphs_used(c, n)) return LB_OK;
     const int launches = graph_launches(c);
     const int parities = (launches & 1) && n >= 2L * launches * steps_per_launch(c) ? 2 : 1;
@@ -694,6 +714,7 @@ lb_status prepare_graphs(lb_ctx* c, long n) {
 // earlier one (those in between stay in LDS).  With several steps per launch the
 // binary model's last step is therefore a launch of its own.
 lb_status run_steps(lb_ctx* c, long n, bool readable = true) {
+    if (lb_status s = check_tiled(c)) return s;
     const int spl = steps_per_launch(c);
     const bool tail = readable && spl > 1 && c->model == LB_BINARY && n > 0;
     if (tail) --n;
@@ -952,6 +973,7 @@ lb_status launch_interface(lb_ctx* c, int record) {
 }
 
 lb_status launch_health(lb_ctx* c) {
+    if (lb_status s = check_tiled(c)) return s;
     if (c->ntiles == 0) return LB_OK;
     const int grid = std::min(c->ntiles, 2048);
     // 512 threads: 8 rows of 64 (tiles have at most 8 rows)
@@ -971,7 +993,8 @@ lb_status cap_index(const lb_ctx* c, int cap) {
 }
 
 lb_status set_active(lb_ctx* c, int k, int on) {
-    if (c->active[k] == on) return LB_OK;
+    if (c->active[k] == on && c->tiled) return LB_OK;
+    c->tiled = false;
     if (!on) {
         c->frozen_buf[k] = c->cur ^ c->L.caps[k].par;
     } else {
@@ -979,7 +1002,10 @@ lb_status set_active(lb_ctx* c, int k, int on) {
     }
     c->active[k] = on;
     c->L.caps[k].active = on;
+    const bool stale = c->caps_stale;
+    c->caps_stale = true;
     HIP_TRY(hipMemcpyAsync(&c->d_caps[k], &c->L.caps[k], sizeof(CapDev), hipMemcpyHostToDevice, c->stream));
+    c->caps_stale = stale;
     return upload_tiles(c);
 }
 
@@ -1318,6 +1344,8 @@ lb_status lb_load(lb_ctx* c, const void* host_buf, size_t bytes) {
     std::memcpy(act.data(), p + sizeof h, sizeof(int) * c->n);
     const float* src = (const float*)(p + sizeof h + sizeof(int) * c->n);
     // every capillary reads arena cur after the load
+    c->caps_stale = true;
+    c->tiled = false;
     for (int k = 0; k < c->n; ++k) {
         CapDev& d = c->L.caps[k];
         const long long nf = region_floats(c, k);
@@ -1338,7 +1366,6 @@ lb_status lb_load(lb_ctx* c, const void* host_buf, size_t bytes) {
     if (h.mstore != c->mstore)
         if (lb_status s = convert_arena(c, c->cur, c->mstore)) return s;
     HIP_TRY(hipStreamSynchronize(c->stream));
-    HIP_TRY(hipMemcpyAsync(c->d_caps, c->L.caps.data(), sizeof(CapDev) * c->n, hipMemcpyHostToDevice, c->stream));
     c->t = (long)h.t;
     c->unstable = 0;
     return upload_tiles(c);
@@ -1366,9 +1393,10 @@ lb_status lb_set_launch_config(lb_ctx* c, const lb_launch_config* cfg) {
     if (ch != 0 && (ch < LB_MIN_CHUNK || ch > 4096))
         return fail(LB_EINVAL, "chunk_rows must be 0 or in 4..4096");
     const bool retile = r != c->cfg.tile_rows || cfg->chunk_rows != c->cfg.chunk_rows ||
-                        cfg->schedule != c->cfg.schedule;
+                        cfg->schedule != c->cfg.schedule || !c->tiled;
     c->cfg = *cfg;
     drop_graphs(c);
+    if (retile) c->tiled = false;   // (also if the conversion below fails)
     if (lb_status s = set_storage(c, cfg->schedule == 6 ? 1 : 0)) return s;
     if (retile) return upload_tiles(c);
     return LB_OK;

@@ -59,12 +59,59 @@ static int graphs_outlive_their_replays() {
     return 0;
 }
 
+// A table upload that fails leaves a context that refuses to step, until the call
+// that set it is repeated.
+static int failed_tables_do_not_step() {
+    for (lb_model m : {LB_VDW, LB_BINARY}) {
+        lb_ctx* c = context(m, {SMALL, SMALL});
+        EXPECT(c);
+        lb_launch_config own, strips;
+        EXPECT(lb_get_launch_config(c, &own) == LB_OK);
+        strips = own;
+        strips.schedule = 3;
+        for (int copy = 0; copy < 3; ++copy) {   // a descriptor, the tiles, the tables of the block kernels
+            EXPECT(lb_step(c, 3) == LB_OK);
+            auto broken = [&]() -> bool {
+                const long t = lb_time(c);
+                return lb_step(c, 5) == LB_ESTATE && lb_time(c) == t && lb_check(c) == LB_ESTATE;
+            };
+            rt.skip_copies = copy, rt.fail_copies = 1;
+            EXPECT(lb_batch_retire(c, 0) == LB_EDEVICE && broken());
+            EXPECT(lb_batch_retire(c, 0) == LB_OK && lb_step(c, 5) == LB_OK && lb_check(c) == LB_OK);
+            rt.skip_copies = copy, rt.fail_copies = 1;
+            EXPECT(lb_batch_revive(c, 0) == LB_EDEVICE && broken());
+            EXPECT(lb_batch_revive(c, 0) == LB_OK);
+        }
+        for (int copy = 0; copy < (m == LB_BINARY ? 3 : 2); ++copy) {   // (descriptors of a changed storage)
+            EXPECT(lb_set_launch_config(c, &strips) == LB_OK);
+            rt.skip_copies = copy, rt.fail_copies = 1;
+            EXPECT(lb_set_launch_config(c, &own) == LB_EDEVICE);
+            EXPECT(lb_step(c, 5) == LB_ESTATE);
+            rt.launches.clear();
+            EXPECT(lb_set_launch_config(c, &own) == LB_OK);
+            EXPECT(rt.count("lb_convert") == 0 && c->d_caps[1].mstore == (m == LB_BINARY));
+            EXPECT(lb_step(c, 1) == LB_OK && rt.count("lb_block") == 1);
+        }
+        std::vector<char> image(lb_checkpoint_bytes(c));
+        EXPECT(lb_save(c, image.data(), image.size()) == LB_OK);
+        const int copies = m == LB_BINARY ? 7 : 5;   // populations (and phi) of two, descriptors, tiles, table
+        for (int copy = 0; copy < copies; ++copy) {
+            rt.skip_copies = copy, rt.fail_copies = 1;
+            EXPECT(lb_load(c, image.data(), image.size()) == LB_EDEVICE && lb_step(c, 5) == LB_ESTATE);
+            EXPECT(lb_load(c, image.data(), image.size()) == LB_OK && lb_step(c, 1) == LB_OK);
+        }
+        lb_free(c);
+    }
+    return 0;
+}
+
 int main(int argc, char** argv) {
     const struct {
         const char* name;
         int (*run)();
     } checks[] = {
         {"graphs_outlive_their_replays", graphs_outlive_their_replays},
+        {"failed_tables_do_not_step", failed_tables_do_not_step},
     };
     for (const auto& k : checks)
         if (argc == 2 && std::string(argv[1]) == k.name) return k.run();

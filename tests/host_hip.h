@@ -24,7 +24,8 @@ struct HostRuntime {
     std::vector<Launched> launches;
     int mallocs = 0;              // device allocations so far
     int fail_mallocs = 0;         // that many of the next device allocations fail
-    int fail_copies = 0;          // that many of the next copies fail
+    int skip_copies = 0;          // that many copies succeed before
+    int fail_copies = 0;          // that many of the next ones fail
     std::vector<unsigned> pinned_flags, event_flags;
     int captures = 0, replays = 0;
     bool pending = false;         // work was enqueued and not waited for
@@ -93,7 +94,9 @@ hipError_t hipHostFree(void* p) {
     return hipSuccess;
 }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
-    if (rt.fail_copies > 0) {
+    if (rt.skip_copies > 0) {
+        --rt.skip_copies;
+    } else if (rt.fail_copies > 0) {
         --rt.fail_copies;
         return hipErrorUnknown;
     }
