@@ -97,7 +97,7 @@ typedef struct lb_ctx lb_ctx;
 const char* lb_last_error(void);
 
 /* Device bytes needed by lb_init for these parameters and this geometry
- * (two FP32 population buffers, descriptors, tile table, l(t) history).
+ * (two FP32 population buffers, descriptors, launch tables, l(t) history).
  * Returns 0 for invalid arguments. */
 size_t lb_state_bytes(const lb_params* p, const lb_geometry* g);
 

@@ -2,7 +2,7 @@
 //
 // A context holds one or more capillaries ("a batch") of the same model in a
 // single device allocation:
-//   [CapDev table][tile table][l_now][l history][history steps][history count]
+//   [CapDev table][tile table][strip table][tile table of the block kernels][l_now][l history][history steps][history count]
 //   [health flags][population arena A][population arena B]
 // Every capillary owns a region of each arena: 9 FP32 planes of shifted f and,
 // for the binary model, one plane of phi, each plane ny x pitch with pitch = nx
@@ -136,7 +136,8 @@ struct Layout {
     long long fluid = 0;
     int max_tiles = 0;
     int max_strips = 0;
-    size_t off_strips = 0;
+    size_t max_blocks = 0;
+    size_t off_strips = 0, off_blocks = 0;
     size_t off_caps, off_tiles, off_lnow, off_hist, off_hist_t, off_hist_n, off_flags, off_arena0, off_arena1,
         total;
 };
@@ -259,6 +260,8 @@ lb_status make_layout(int n, const lb_params* P, const lb_geometry* G, Layout& L
         // room for the strip table of either width at any chunking
         const std::vector<lb_geometry> gv(G, G + n);
         L.max_strips = std::max(strip_capacity(gv, STRIP_OUT), strip_capacity(gv, WIDE_OUT));
+        L.max_blocks = block_capacity(gv, P[0].model == LB_VDW);
+        if (L.max_blocks > 0x7ffffff0u) return fail(LB_EINVAL, "tile table too large");
     }
     size_t o = 0;
     L.off_caps = o;
@@ -267,6 +270,8 @@ lb_status make_layout(int n, const lb_params* P, const lb_geometry* G, Layout& L
     o = align_up(o + sizeof(TileDev) * (size_t)L.max_tiles);
     L.off_strips = o;
     o = align_up(o + sizeof(StripDev) * (size_t)L.max_strips);
+    L.off_blocks = o;
+    o = align_up(o + sizeof(BlockDev) * L.max_blocks);
     L.off_lnow = o;
     o = align_up(o + sizeof(float) * n);
     L.off_hist = o;
@@ -328,8 +333,7 @@ struct lb_ctx {
     StripDev* d_strips = nullptr;
     int nstrips = 0;
     int xcd_start[9] = {};    // strip runs of the 8 XCDs
-    BlockDev* d_blocks = nullptr;   // tiles of the block kernels (an allocation of its own)
-    size_t blocks_cap = 0;
+    BlockDev* d_blocks = nullptr;   // tiles of the block kernels
     int nblocks = 0;
     int block_k = 0;          // steps per launch of the block kernels; 0: other schedules
     int block_shape = 0;
@@ -423,19 +427,10 @@ bool uses_blocks(const lb_ctx* c) { return c->cfg.schedule == (c->model == LB_VD
 lb_status upload_blocks(lb_ctx* c) {
     const bool vdw = c->model == LB_VDW;
     const BlockPlan p = plan_block_tiles(c->G, c->active, vdw);
-    if (p.tiles > 0x7ffffff0u) return fail(LB_EINVAL, "tile table too large");
     if (p.tiles == 0) return LB_OK;   // every capillary is retired
     std::vector<BlockDev> t;
     build_blocks(c->G, c->active, p.K, block_rx(p.shape), block_ry(p.shape, vdw), block_align(p.shape, vdw), &t);
-    if (t.size() > c->blocks_cap) {
-        HIP_TRY(hipStreamSynchronize(c->stream));
-        (void)hipFree(c->d_blocks);
-        c->d_blocks = nullptr;
-        c->blocks_cap = 0;
-        if (hipMalloc(&c->d_blocks, sizeof(BlockDev) * t.size()) != hipSuccess)
-            return fail(LB_ENOMEM, "device allocation of the tile table failed");
-        c->blocks_cap = t.size();
-    }
+    if (t.size() > c->L.max_blocks) return fail(LB_EINVAL, "tile table overflow");
     HIP_TRY(hipMemcpyAsync(c->d_blocks, t.data(), sizeof(BlockDev) * t.size(), hipMemcpyHostToDevice, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     c->nblocks = (int)t.size();
@@ -808,6 +803,7 @@ lb_status create(lb_ctx** out, int n, const lb_params* P, const lb_geometry* G, 
     c->d_caps = (CapDev*)(c->mem + c->L.off_caps);
     c->d_tiles = (TileDev*)(c->mem + c->L.off_tiles);
     c->d_strips = (StripDev*)(c->mem + c->L.off_strips);
+    c->d_blocks = (BlockDev*)(c->mem + c->L.off_blocks);
     c->d_lnow = (float*)(c->mem + c->L.off_lnow);
     c->d_hist = (float*)(c->mem + c->L.off_hist);
     c->d_hist_t = (long long*)(c->mem + c->L.off_hist_t);
@@ -1513,7 +1509,6 @@ void lb_free(lb_ctx* c) {
     for (hipEvent_t e : c->pin_ev)
         if (e) (void)hipEventDestroy(e);
     if (c->pin) pin_give(c->pin);
-    (void)hipFree(c->d_blocks);
     if (c->own_mem && c->mem) (void)hipFree(c->mem);
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
     delete c;

@@ -94,6 +94,34 @@ inline int block_ry(int shape, bool vdw) { return shape == 2 || (shape == 1 && !
 // columns than that gains (the 256-capillary sweep: 422 against 374 us).
 inline int block_align(int shape, bool vdw) { return shape == 1 && vdw ? 16 : 1; }
 
+// What a launch of shape `shape` costs at K steps, kmin <= K <= kmax (see plan_block_tiles).
+struct BlockCost {
+    int shape, kmin, kmax;
+    double launch, launch_k, tile, tile_k;
+};
+constexpr BlockCost BLOCK_COST_BINARY[BLOCK_SHAPES] = {
+    {0, 2, 6, 2.8, 1.64, 2.57, 0.44}, {1, 2, 3, 4.4, 2.07, 3.95, 0.46}, {2, 2, 5, 2.5, 1.47, 2.02, 0.30}};
+constexpr BlockCost BLOCK_COST_VDW[BLOCK_SHAPES] = {
+    {0, 2, 6, 2.84, 1.10, 2.85, 0.06}, {1, 2, 4, 3.64, 1.83, 4.79, 0.23}, {2, 2, 5, 2.66, 0.99, 2.09, 0.05}};
+inline const BlockCost* block_costs(bool vdw) { return vdw ? BLOCK_COST_VDW : BLOCK_COST_BINARY; }
+
+// Tiles that a table may need, whatever the plan and the set of active capillaries:
+// the most that any plan cuts each capillary into.
+inline size_t block_capacity(const std::vector<lb_geometry>& G, bool vdw) {
+    size_t total = 0;
+    for (const lb_geometry& g : G) {
+        size_t most = 0;
+        for (int i = 0; i < BLOCK_SHAPES; ++i) {
+            const BlockCost& c = block_costs(vdw)[i];
+            for (int K = c.kmin; K <= c.kmax; ++K)
+                most = std::max(most, build_blocks({g}, {1}, K, block_rx(c.shape), block_ry(c.shape, vdw),
+                                                   block_align(c.shape, vdw), nullptr));
+        }
+        total += most;
+    }
+    return total;
+}
+
 // The cheapest plan.  A launch costs its own latency, which grows with K, and so much
 // for every further tile of a CU: whole rounds of 256 tiles up to the second (the 5 x
 // 512 x 64 batch of the binary model: 250 tiles at K = 3 3.05 us a step, 290 at K = 4
@@ -106,17 +134,10 @@ inline int block_align(int shape, bool vdw) { return shape == 1 && vdw ? 16 : 1;
 // K = 2, 10.6 at K = 4), the large shape, with fewer halo nodes, from about a million
 // nodes (binary 8192 x 1024: 79 against 102 us).
 inline BlockPlan plan_block_tiles(const std::vector<lb_geometry>& G, const std::vector<int>& active, bool vdw) {
-    struct Cost {
-        int shape, kmin, kmax;
-        double launch, launch_k, tile, tile_k;
-    };
-    static const Cost binary[] = {
-        {0, 2, 6, 2.8, 1.64, 2.57, 0.44}, {1, 2, 3, 4.4, 2.07, 3.95, 0.46}, {2, 2, 5, 2.5, 1.47, 2.02, 0.30}};
-    static const Cost van[] = {
-        {0, 2, 6, 2.84, 1.10, 2.85, 0.06}, {1, 2, 4, 3.64, 1.83, 4.79, 0.23}, {2, 2, 5, 2.66, 0.99, 2.09, 0.05}};
     BlockPlan best{0, 0, 0};
     double cheapest = 0.0;
-    for (const Cost& c : vdw ? van : binary)
+    for (int i = 0; i < BLOCK_SHAPES; ++i) {
+        const BlockCost& c = block_costs(vdw)[i];
         for (int K = c.kmin; K <= c.kmax; ++K) {
             const size_t n = build_blocks(G, active, K, block_rx(c.shape), block_ry(c.shape, vdw),
                                           block_align(c.shape, vdw), nullptr);
@@ -127,6 +148,7 @@ inline BlockPlan plan_block_tiles(const std::vector<lb_geometry>& G, const std::
                 cheapest = us;
             }
         }
+    }
     return best;
 }
 

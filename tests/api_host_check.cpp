@@ -105,6 +105,58 @@ static int failed_tables_do_not_step() {
     return 0;
 }
 
+// A context allocates no device memory beyond its state: none with a caller's
+// d_state, and none when capillaries retire, return or load, or launch
+// configurations change, whatever the plan becomes.
+static int no_device_memory_beside_the_state() {
+    unsigned s = 1;
+    auto rnd = [&](int lo, int hi) {
+        s = s * 1664525u + 1013904223u;
+        return lo + (int)((s >> 8) % (unsigned)(hi - lo + 1));
+    };
+    for (int pass = 0; pass < 30; ++pass) {
+        const lb_model m = pass % 2 ? LB_VDW : LB_BINARY;
+        std::vector<lb_geometry> g;
+        for (int n = rnd(2, 24); n > 0; --n) {
+            const int ny = rnd(20, 120), nx = rnd(60, 900), h = rnd(8, ny - 4), len = rnd(20, nx - 20);
+            g.push_back({nx, ny, rnd(1, nx - len), len, h, rnd(1, ny - 1 - h)});
+        }
+        lb_ctx* c = context(m, g);
+        EXPECT(c);
+        const int before = rt.mallocs;
+        std::vector<char> image(lb_checkpoint_bytes(c));
+        EXPECT(lb_save(c, image.data(), image.size()) == LB_OK);
+        lb_launch_config cfg, strips;
+        EXPECT(lb_get_launch_config(c, &cfg) == LB_OK);
+        strips = cfg;
+        strips.schedule = 5;
+        for (int k = 0; k < 40; ++k) {
+            const int cap = rnd(0, (int)g.size() - 1);
+            EXPECT((rnd(0, 2) ? lb_batch_retire(c, cap) : lb_batch_revive(c, cap)) == LB_OK);
+            if (k % 10 == 5) {
+                EXPECT(lb_set_launch_config(c, &strips) == LB_OK && lb_set_launch_config(c, &cfg) == LB_OK);
+                EXPECT(lb_load(c, image.data(), image.size()) == LB_OK);
+            }
+            EXPECT(lb_step(c, 1) == LB_OK);
+        }
+        EXPECT(rt.mallocs == before);
+        lb_free(c);
+
+        // in the caller's memory, which is not touched past its end
+        const lb_params p = params(m);
+        const size_t bytes = lb_state_bytes(&p, &g[0]);
+        char* mem = (char*)std::aligned_alloc(4096, (bytes + 8191) / 4096 * 4096);
+        std::memset(mem + bytes, 0x5a, 4096);
+        const std::vector<double> q((size_t)g[0].nx * g[0].ny, m == LB_VDW ? 3.0 : 0.5);
+        EXPECT(lb_init(&c, &p, &g[0], q.data(), mem, bytes, nullptr) == LB_OK);
+        EXPECT(lb_step(c, 9) == LB_OK && rt.mallocs == before);
+        lb_free(c);
+        for (int k = 0; k < 4096; ++k) EXPECT(mem[bytes + k] == 0x5a);
+        std::free(mem);
+    }
+    return 0;
+}
+
 int main(int argc, char** argv) {
     const struct {
         const char* name;
@@ -112,6 +164,7 @@ int main(int argc, char** argv) {
     } checks[] = {
         {"graphs_outlive_their_replays", graphs_outlive_their_replays},
         {"failed_tables_do_not_step", failed_tables_do_not_step},
+        {"no_device_memory_beside_the_state", no_device_memory_beside_the_state},
     };
     for (const auto& k : checks)
         if (argc == 2 && std::string(argv[1]) == k.name) return k.run();
