@@ -136,28 +136,23 @@ struct Layout {
     long long fluid = 0;
     int max_tiles = 0;
     int max_strips = 0;
+    std::vector<BlockCounts> blocks;   // tiles of each capillary under every plan
     size_t max_blocks = 0;
     size_t off_strips = 0, off_blocks = 0;
     size_t off_caps, off_tiles, off_lnow, off_hist, off_hist_t, off_hist_n, off_flags, off_arena0, off_arena1,
         total;
 };
 
+// Whether the tile of `rows` rows at (x0, y0) holds a fluid node.
+bool tile_has_fluid(const lb_geometry& g, int x0, int y0, int rows) {
+    if (g.tube_len <= 0 || x0 < g.x_in || std::min(x0 + TILE_W, g.nx) > g.x_in + g.tube_len) return true;
+    return std::max(y0, g.y0) < std::min(std::min(y0 + rows, g.ny), g.y0 + g.tube_h);
+}
+
 int count_tiles(const lb_geometry& g, int rows) {
     int n = 0;
     for (int y0 = 0; y0 < g.ny; y0 += rows)
-        for (int x0 = 0; x0 < g.nx; x0 += TILE_W) {
-            bool any = false;
-            for (int y = y0; y < std::min(y0 + rows, g.ny) && !any; ++y) {
-                const bool wall_row = g.tube_len > 0 && (y < g.y0 || y >= g.y0 + g.tube_h);
-                if (!wall_row) {
-                    any = true;
-                    break;
-                }
-                const int xe = std::min(x0 + TILE_W, g.nx);
-                if (x0 < g.x_in || xe > g.x_in + g.tube_len) any = true;
-            }
-            n += any;
-        }
+        for (int x0 = 0; x0 < g.nx; x0 += TILE_W) n += tile_has_fluid(g, x0, y0, rows);
     return n;
 }
 
@@ -168,16 +163,8 @@ void build_tiles(const std::vector<lb_geometry>& G, const std::vector<int>& acti
         if (!active[k]) continue;
         const lb_geometry& g = G[k];
         for (int y0 = 0; y0 < g.ny; y0 += rows)
-            for (int x0 = 0; x0 < g.nx; x0 += TILE_W) {
-                bool any = false;
-                for (int y = y0; y < std::min(y0 + rows, g.ny) && !any; ++y) {
-                    const bool wall_row = g.tube_len > 0 && (y < g.y0 || y >= g.y0 + g.tube_h);
-                    if (!wall_row) any = true;
-                    const int xe = std::min(x0 + TILE_W, g.nx);
-                    if (x0 < g.x_in || xe > g.x_in + g.tube_len) any = true;
-                }
-                if (any) out.push_back(TileDev{(int)k, x0, y0, std::min(rows, g.ny - y0)});
-            }
+            for (int x0 = 0; x0 < g.nx; x0 += TILE_W)
+                if (tile_has_fluid(g, x0, y0, rows)) out.push_back(TileDev{(int)k, x0, y0, std::min(rows, g.ny - y0)});
     }
 }
 
@@ -260,7 +247,8 @@ lb_status make_layout(int n, const lb_params* P, const lb_geometry* G, Layout& L
         // room for the strip table of either width at any chunking
         const std::vector<lb_geometry> gv(G, G + n);
         L.max_strips = std::max(strip_capacity(gv, STRIP_OUT), strip_capacity(gv, WIDE_OUT));
-        L.max_blocks = block_capacity(gv, P[0].model == LB_VDW);
+        for (const lb_geometry& g : gv) L.blocks.push_back(count_blocks(g, P[0].model == LB_VDW));
+        L.max_blocks = block_capacity(L.blocks);
         if (L.max_blocks > 0x7ffffff0u) return fail(LB_EINVAL, "tile table too large");
     }
     size_t o = 0;
@@ -355,6 +343,8 @@ struct lb_ctx {
     hipEvent_t pin_ev[2] = {nullptr, nullptr};   // a half of it is written
     long timed_steps = 0;
     int unstable = 0;
+    std::vector<TileDev> h_tiles;     // the tables as uploaded (retiring builds them again: the
+    std::vector<BlockDev> h_blocks;   // pages of 3 MB for 256 capillaries cost as much as the rest)
     bool caps_stale = false;  // an upload of descriptors failed
     bool tiled = false;       // the tables on the device are those of cfg and the active capillaries
     bool any_force = false;   // some capillary has a body force (row sweeps keep the forcing terms)
@@ -424,15 +414,16 @@ int steps_per_launch(const lb_ctx* c) { return c->block_k > 0 ? c->block_k : (c-
 // (lb_block.h); the others sweep rows or single-step tiles.
 bool uses_blocks(const lb_ctx* c) { return c->cfg.schedule == (c->model == LB_VDW ? 4 : 6); }
 
+// (the caller waits for the copy)
 lb_status upload_blocks(lb_ctx* c) {
+    std::vector<BlockDev>& t = c->h_blocks;
     const bool vdw = c->model == LB_VDW;
-    const BlockPlan p = plan_block_tiles(c->G, c->active, vdw);
+    const BlockPlan p = plan_block_tiles(c->L.blocks, c->active, vdw);
     if (p.tiles == 0) return LB_OK;   // every capillary is retired
-    std::vector<BlockDev> t;
+    t.reserve(p.tiles);
     build_blocks(c->G, c->active, p.K, block_rx(p.shape), block_ry(p.shape, vdw), block_align(p.shape, vdw), &t);
     if (t.size() > c->L.max_blocks) return fail(LB_EINVAL, "tile table overflow");
     HIP_TRY(hipMemcpyAsync(c->d_blocks, t.data(), sizeof(BlockDev) * t.size(), hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
     c->nblocks = (int)t.size();
     c->block_k = p.K;
     c->block_shape = p.shape;
@@ -505,7 +496,7 @@ lb_status upload_tiles(lb_ctx* c) {
     if (c->caps_stale)
         if (lb_status s = upload_caps(c)) return s;
     c->nstrips = c->nblocks = c->block_k = 0;
-    std::vector<TileDev> tiles;
+    std::vector<TileDev>& tiles = c->h_tiles;
     build_tiles(c->G, c->active, c->cfg.tile_rows, tiles);
     if ((int)tiles.size() > c->L.max_tiles) return fail(LB_EINVAL, "tile table overflow");
     c->ntiles = (int)tiles.size();
@@ -520,9 +511,9 @@ lb_status upload_tiles(lb_ctx* c) {
     if (!strips.empty())
         HIP_TRY(hipMemcpyAsync(c->d_strips, strips.data(), sizeof(StripDev) * strips.size(), hipMemcpyHostToDevice,
                                c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
     if (uses_blocks(c))
         if (lb_status s = upload_blocks(c)) return s;
+    HIP_TRY(hipStreamSynchronize(c->stream));
     c->tiled = true;
     return LB_OK;
 }

@@ -2,6 +2,7 @@
 // each workgroup.  Host code only, so that it also builds without HIP.
 #pragma once
 #include <algorithm>
+#include <array>
 #include <vector>
 
 #include "lbcap.h"
@@ -105,20 +106,27 @@ constexpr BlockCost BLOCK_COST_VDW[BLOCK_SHAPES] = {
     {0, 2, 6, 2.84, 1.10, 2.85, 0.06}, {1, 2, 4, 3.64, 1.83, 4.79, 0.23}, {2, 2, 5, 2.66, 0.99, 2.09, 0.05}};
 inline const BlockCost* block_costs(bool vdw) { return vdw ? BLOCK_COST_VDW : BLOCK_COST_BINARY; }
 
+// Every plan has a place: shape i at K steps is place 6 i + K - kmin.
+constexpr int BLOCK_PLANS = 6 * BLOCK_SHAPES;
+using BlockCounts = std::array<unsigned, BLOCK_PLANS>;
+
+// Tiles that each plan cuts a lattice into.
+inline BlockCounts count_blocks(const lb_geometry& g, bool vdw) {
+    BlockCounts n{};
+    for (int i = 0; i < BLOCK_SHAPES; ++i) {
+        const BlockCost& c = block_costs(vdw)[i];
+        for (int K = c.kmin; K <= c.kmax; ++K)
+            n[6 * i + K - c.kmin] = (unsigned)build_blocks({g}, {1}, K, block_rx(c.shape), block_ry(c.shape, vdw),
+                                                           block_align(c.shape, vdw), nullptr);
+    }
+    return n;
+}
+
 // Tiles that a table may need, whatever the plan and the set of active capillaries:
 // the most that any plan cuts each capillary into.
-inline size_t block_capacity(const std::vector<lb_geometry>& G, bool vdw) {
+inline size_t block_capacity(const std::vector<BlockCounts>& counts) {
     size_t total = 0;
-    for (const lb_geometry& g : G) {
-        size_t most = 0;
-        for (int i = 0; i < BLOCK_SHAPES; ++i) {
-            const BlockCost& c = block_costs(vdw)[i];
-            for (int K = c.kmin; K <= c.kmax; ++K)
-                most = std::max(most, build_blocks({g}, {1}, K, block_rx(c.shape), block_ry(c.shape, vdw),
-                                                   block_align(c.shape, vdw), nullptr));
-        }
-        total += most;
-    }
+    for (const BlockCounts& n : counts) total += *std::max_element(n.begin(), n.end());
     return total;
 }
 
@@ -133,14 +141,19 @@ inline size_t block_capacity(const std::vector<lb_geometry>& G, bool vdw) {
 // against 2.06); a small K when halos cost throughput (binary 4096 x 256: 8.2 us at
 // K = 2, 10.6 at K = 4), the large shape, with fewer halo nodes, from about a million
 // nodes (binary 8192 x 1024: 79 against 102 us).
-inline BlockPlan plan_block_tiles(const std::vector<lb_geometry>& G, const std::vector<int>& active, bool vdw) {
+//
+// counts: count_blocks of each capillary, kept by the caller, who plans again whenever
+// one retires (counting all plans of 256 capillaries takes the host 3 ms, summing 10 us).
+inline BlockPlan plan_block_tiles(const std::vector<BlockCounts>& counts, const std::vector<int>& active, bool vdw) {
+    std::array<size_t, BLOCK_PLANS> total{};
+    for (size_t k = 0; k < counts.size(); ++k)
+        for (int i = 0; i < BLOCK_PLANS && active[k]; ++i) total[i] += counts[k][i];
     BlockPlan best{0, 0, 0};
     double cheapest = 0.0;
     for (int i = 0; i < BLOCK_SHAPES; ++i) {
         const BlockCost& c = block_costs(vdw)[i];
         for (int K = c.kmin; K <= c.kmax; ++K) {
-            const size_t n = build_blocks(G, active, K, block_rx(c.shape), block_ry(c.shape, vdw),
-                                          block_align(c.shape, vdw), nullptr);
+            const size_t n = total[6 * i + K - c.kmin];
             const double over = n <= 512 ? (n > 256 ? 1.0 : 0.0) : n / 256.0 - 0.5;
             const double us = (c.launch + c.launch_k * K + (c.tile + c.tile_k * K) * over) / K;
             if (best.K == 0 || us < cheapest) {
@@ -150,6 +163,11 @@ inline BlockPlan plan_block_tiles(const std::vector<lb_geometry>& G, const std::
         }
     }
     return best;
+}
+inline BlockPlan plan_block_tiles(const std::vector<lb_geometry>& G, const std::vector<int>& active, bool vdw) {
+    std::vector<BlockCounts> counts;
+    for (const lb_geometry& g : G) counts.push_back(count_blocks(g, vdw));
+    return plan_block_tiles(counts, active, vdw);
 }
 
 }  // namespace lbk

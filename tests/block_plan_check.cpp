@@ -1,0 +1,47 @@
+// Checks of the block kernels' planning on the host.
+#include <cstdio>
+#include <vector>
+
+#include "lb_block_table.h"
+
+using namespace lbk;
+
+// The plan made from the counts that a context keeps is the one made by cutting the
+// active lattices anew, and the table it stands for fits what the context reserves.
+static int kept_counts() {
+    unsigned s = 5;
+    auto rnd = [&](int lo, int hi) {
+        s = s * 1664525u + 1013904223u;
+        return lo + (int)((s >> 8) % (unsigned)(hi - lo + 1));
+    };
+    for (int pass = 0; pass < 400; ++pass) {
+        const bool vdw = pass % 2;
+        std::vector<lb_geometry> G;
+        std::vector<BlockCounts> counts;
+        for (int n = rnd(1, 30); n > 0; --n) {
+            lb_geometry g{rnd(3, pass % 7 ? 400 : 4000), rnd(5, 140), 0, 0, 0, 0};
+            if (n % 8) {
+                g.tube_len = rnd(1, g.nx);
+                g.x_in = rnd(0, g.nx - g.tube_len);
+                g.tube_h = rnd(3, g.ny - 2);
+                g.y0 = rnd(1, g.ny - 1 - g.tube_h);
+            }
+            G.push_back(g);
+            counts.push_back(count_blocks(g, vdw));
+        }
+        for (int k = 0; k < 10; ++k) {
+            std::vector<int> active(G.size());
+            for (int& a : active) a = rnd(0, 3) > 0;
+            const BlockPlan a = plan_block_tiles(counts, active, vdw), b = plan_block_tiles(G, active, vdw);
+            const size_t n =
+                build_blocks(G, active, a.K, block_rx(a.shape), block_ry(a.shape, vdw), block_align(a.shape, vdw), nullptr);
+            if (a.shape != b.shape || a.K != b.K || a.tiles != n || n > block_capacity(counts)) {
+                std::printf("plan from counts: shape %d K %d, %zu tiles, %zu cut\n", a.shape, a.K, a.tiles, n);
+                return 1;
+            }
+        }
+    }
+    return 0;
+}
+
+int main() { return kept_counts(); }
