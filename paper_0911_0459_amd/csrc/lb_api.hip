@@ -143,28 +143,41 @@ struct Layout {
         total;
 };
 
-// Whether the tile of `rows` rows at (x0, y0) holds a fluid node.
-bool tile_has_fluid(const lb_geometry& g, int x0, int y0, int rows) {
-    if (g.tube_len <= 0 || x0 < g.x_in || std::min(x0 + TILE_W, g.nx) > g.x_in + g.tube_len) return true;
-    return std::max(y0, g.y0) < std::min(std::min(y0 + rows, g.ny), g.y0 + g.tube_h);
-}
+// The tiles with fluid nodes in the tile row that begins at y0, as runs of columns
+// [0, a) and [b, n) of tiles.
+struct TileRow {
+    int a, b, n;
+    TileRow(const lb_geometry& g, int y0, int rows) {
+        n = (g.nx + TILE_W - 1) / TILE_W;
+        const int te = g.x_in + g.tube_len;
+        const bool channel = std::max(y0, g.y0) < std::min(std::min(y0 + rows, g.ny), g.y0 + g.tube_h);
+        a = g.tube_len <= 0 || channel ? n : (g.x_in + TILE_W - 1) / TILE_W;
+        b = std::max(a, te < g.nx ? te / TILE_W : n);
+    }
+    int count() const { return n - (b - a); }
+};
 
 int count_tiles(const lb_geometry& g, int rows) {
     int n = 0;
-    for (int y0 = 0; y0 < g.ny; y0 += rows)
-        for (int x0 = 0; x0 < g.nx; x0 += TILE_W) n += tile_has_fluid(g, x0, y0, rows);
+    for (int y0 = 0; y0 < g.ny; y0 += rows) n += TileRow(g, y0, rows).count();
     return n;
 }
 
 void build_tiles(const std::vector<lb_geometry>& G, const std::vector<int>& active, int rows,
                  std::vector<TileDev>& out) {
-    out.clear();
+    size_t n = 0;
+    for (size_t k = 0; k < G.size(); ++k) n += active[k] ? (size_t)count_tiles(G[k], rows) : 0;
+    out.resize(n);
+    TileDev* at = out.data();
     for (size_t k = 0; k < G.size(); ++k) {
         if (!active[k]) continue;
         const lb_geometry& g = G[k];
-        for (int y0 = 0; y0 < g.ny; y0 += rows)
-            for (int x0 = 0; x0 < g.nx; x0 += TILE_W)
-                if (tile_has_fluid(g, x0, y0, rows)) out.push_back(TileDev{(int)k, x0, y0, std::min(rows, g.ny - y0)});
+        for (int y0 = 0; y0 < g.ny; y0 += rows) {
+            const TileRow r(g, y0, rows);
+            const int h = std::min(rows, g.ny - y0);
+            for (int i = 0; i < r.a; ++i) *at++ = TileDev{(int)k, i * TILE_W, y0, h};
+            for (int i = r.b; i < r.n; ++i) *at++ = TileDev{(int)k, i * TILE_W, y0, h};
+        }
     }
 }
 

@@ -157,6 +157,38 @@ static int no_device_memory_beside_the_state() {
     return 0;
 }
 
+// The single-step tiles are, in order, those with a fluid node.
+static int tiles_with_fluid() {
+    unsigned s = 3;
+    auto rnd = [&](int lo, int hi) {
+        s = s * 1664525u + 1013904223u;
+        return lo + (int)((s >> 8) % (unsigned)(hi - lo + 1));
+    };
+    for (int pass = 0; pass < 2000; ++pass) {
+        lb_geometry g{rnd(3, 400), rnd(5, 90), 0, 0, 0, 0};
+        if (pass % 8) {
+            g.tube_len = rnd(1, g.nx), g.x_in = rnd(0, g.nx - g.tube_len);
+            g.tube_h = rnd(3, g.ny - 2), g.y0 = rnd(1, g.ny - 1 - g.tube_h);
+        }
+        const int rows = 1 << rnd(0, 3);
+        std::vector<TileDev> t;
+        build_tiles({g, g}, {0, 1}, rows, t);
+        size_t at = 0;
+        for (int y0 = 0; y0 < g.ny; y0 += rows)
+            for (int x0 = 0; x0 < g.nx; x0 += TILE_W) {
+                bool fluid = false;
+                const int h = std::min(rows, g.ny - y0);
+                for (int y = y0; y < y0 + h; ++y)
+                    for (int x = x0; x < std::min(x0 + TILE_W, g.nx); ++x) fluid = fluid || !solid_at(g, x, y);
+                if (!fluid) continue;
+                EXPECT(at < t.size() && t[at].cap == 1 && t[at].x0 == x0 && t[at].y0 == y0 && t[at].rows == h);
+                ++at;
+            }
+        EXPECT(at == t.size() && (int)at == count_tiles(g, rows));
+    }
+    return 0;
+}
+
 int main(int argc, char** argv) {
     const struct {
         const char* name;
@@ -164,6 +196,7 @@ int main(int argc, char** argv) {
     } checks[] = {
         {"graphs_outlive_their_replays", graphs_outlive_their_replays},
         {"failed_tables_do_not_step", failed_tables_do_not_step},
+        {"tiles_with_fluid", tiles_with_fluid},
         {"no_device_memory_beside_the_state", no_device_memory_beside_the_state},
     };
     for (const auto& k : checks)
