@@ -63,6 +63,10 @@ bool solid_at(const lb_geometry& g, int x, int y) {
     return y < g.y0 || y >= g.y0 + g.tube_h;
 }
 
+long long fluid_nodes(const lb_geometry& g) {
+    return (long long)g.nx * g.ny - (g.tube_len > 0 ? (long long)g.tube_len * (g.ny - g.tube_h) : 0);
+}
+
 // Every ghost source of the wall rule must be a fluid node.
 bool ghost_sources_fluid(const lb_geometry& g) {
     if (g.tube_len <= 0) return true;
@@ -251,8 +255,7 @@ lb_status make_layout(int n, const lb_params* P, const lb_geometry* G, Layout& L
         }
         c.hist_off = k * LB_HISTORY_CAP;
         L.caps[k] = c;
-        long long solid = g.tube_len > 0 ? (long long)g.tube_len * (g.ny - g.tube_h) : 0;
-        L.fluid += (long long)g.nx * g.ny - solid;
+        L.fluid += fluid_nodes(g);
         L.max_tiles += count_tiles(g, 1);
     }
     L.arena_floats = off;
@@ -338,6 +341,7 @@ struct lb_ctx {
     int nblocks = 0;
     int block_k = 0;          // steps per launch of the block kernels; 0: other schedules
     int block_shape = 0;
+    bool single_rows = false; // single steps go by the row sweep (see rows_for_single_steps)
     float* d_lnow = nullptr;
     float* d_hist = nullptr;
     long long* d_hist_t = nullptr;
@@ -426,6 +430,20 @@ int steps_per_launch(const lb_ctx* c) { return c->block_k > 0 ? c->block_k : (c-
 // Schedules 4 (van der Waals) and 6 advance several steps per launch in tiles
 // (lb_block.h); the others sweep rows or single-step tiles.
 bool uses_blocks(const lb_ctx* c) { return c->cfg.schedule == (c->model == LB_VDW ? 4 : 6); }
+
+// Single steps (the binary model's last one of every call, a remainder) of large
+// contexts go by the wide row sweep over the same storage, bitwise the same: a launch
+// of the tiles takes the halo of K steps for one, and beyond the caches re-reads it.
+// Tiles against rows, us a step: binary 2.3 M fluid nodes 47 / 65, 3.5 M 72 / 75,
+// 4.6 M 110 / 89, 9.2 M 221 / 154, the 256-capillary sweep (33 M) 650 / 500 (a table cut
+// for K = 1: 525); van der Waals 1.2 M 29 / 28, 1.7 M 37 / 35, 2.3 M 48 / 43, 9.2 M
+// 209 / 164.
+bool rows_for_single_steps(const lb_ctx* c) {
+    long long fluid = 0;
+    for (int k = 0; k < c->n; ++k)
+        if (c->active[k]) fluid += fluid_nodes(c->G[k]);
+    return uses_blocks(c) && fluid >= (c->model == LB_VDW ? 1500000 : 4000000);
+}
 
 // (the caller waits for the copy)
 lb_status upload_blocks(lb_ctx* c) {
@@ -516,8 +534,9 @@ lb_status upload_tiles(lb_ctx* c) {
     if (!tiles.empty())
         HIP_TRY(hipMemcpyAsync(c->d_tiles, tiles.data(), sizeof(TileDev) * tiles.size(), hipMemcpyHostToDevice,
                                c->stream));
+    c->single_rows = rows_for_single_steps(c);
     std::vector<StripDev> strips;
-    if (!uses_blocks(c))
+    if (!uses_blocks(c) || c->single_rows)
         build_strips(c->G, c->active, c->cfg.chunk_rows, strip_width(c->cfg), 2, &strips, nullptr, c->xcd_start);
     if ((int)strips.size() > c->L.max_strips) return fail(LB_EINVAL, "strip table overflow");
     c->nstrips = (int)strips.size();
@@ -579,6 +598,8 @@ void launch_strip_f(lb_ctx* c, const StripArgs& a, int grid, bool fused) {
     } else {
         if (fused)
             hipLaunchKernelGGL((lb_wide2_bin<MT, CT, ST, FORCE>), dim3(grid), dim3(WIDE_THREADS), 0, c->stream, a);
+        else if (c->cfg.schedule == 6)
+            hipLaunchKernelGGL((lb_wmom_bin<MT, CT, ST, FORCE>), dim3(grid), dim3(WIDE_THREADS), 0, c->stream, a);
         else if (wide)
             hipLaunchKernelGGL((lb_wide_bin<MT, CT, ST, FORCE>), dim3(grid), dim3(WIDE_THREADS), 0, c->stream, a);
         else
@@ -655,9 +676,10 @@ void enqueue_step(lb_ctx* c, bool init, bool fused = false) {
     }
 }
 
-// Enqueue one launch of `steps` steps (at most steps_per_launch).
+// Enqueue one launch of `steps` steps (at most steps_per_launch).  With tiles and
+// single_rows the strips are those of the wide sweep over the tiles' storage.
 void enqueue_launch(lb_ctx* c, int steps) {
-    if (uses_blocks(c))
+    if (uses_blocks(c) && !(steps == 1 && c->single_rows))
         enqueue_block(c, steps);
     else
         enqueue_step(c, false, steps == 2);

@@ -10,7 +10,7 @@
 // on the same FP32 values: what a step leaves in LDS for the next one is rounded
 // exactly as it would be stored), so the fields do not depend on K, on the tiling
 // or on how steps are grouped into launches, and are bitwise those of lb_wide_vdw
-// and, for the binary model, of the single-step sweep this kernel replaced.
+// and lb_wmom_bin, which take the single steps of large contexts.
 //
 // Per step two phases, each ended by an LDS-only barrier; with m = 2 (steps left
 // after this one), on nodes up to a distance from the tile:

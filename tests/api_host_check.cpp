@@ -189,6 +189,35 @@ static int tiles_with_fluid() {
     return 0;
 }
 
+// Single steps of large contexts go by the row sweep, all others by the tiles; what
+// is large is counted over the active capillaries.
+static int single_steps_of_large_contexts() {
+    const lb_geometry part{1500, 500, 100, 1000, 200, 150}, large{3000, 1500, 700, 1000, 1400, 50};
+    for (lb_model m : {LB_VDW, LB_BINARY}) {
+        const char* rows = m == LB_VDW ? "lb_wide_vdw" : "lb_wmom_bin";
+        lb_ctx* c = context(m, {large, part});
+        EXPECT(c);
+        lb_launch_config cfg;
+        EXPECT(lb_get_launch_config(c, &cfg) == LB_OK);
+        cfg.graph_steps = 0;
+        EXPECT(lb_set_launch_config(c, &cfg) == LB_OK);
+        const int K = c->block_k;
+        auto launches = [&](long steps, int tiles, int sweeps) {
+            rt.launches.clear();
+            return lb_step(c, steps) == LB_OK && rt.count("lb_block") == tiles && rt.count(rows) == sweeps &&
+                   (int)rt.launches.size() == tiles + sweeps;
+        };
+        EXPECT(launches(1, 0, 1));
+        // K steps, and (binary) the last one of the call
+        EXPECT(m == LB_VDW ? launches(K, 1, 0) && launches(K + 1, 1, 1) : launches(K + 1, 1, 1) && launches(K + 2, 1, 2));
+        EXPECT(lb_batch_retire(c, 0) == LB_OK);   // 0.45 M nodes are left
+        EXPECT(launches(1, 1, 0));
+        EXPECT(lb_batch_revive(c, 0) == LB_OK && launches(1, 0, 1));
+        lb_free(c);
+    }
+    return 0;
+}
+
 int main(int argc, char** argv) {
     const struct {
         const char* name;
@@ -196,6 +225,7 @@ int main(int argc, char** argv) {
     } checks[] = {
         {"graphs_outlive_their_replays", graphs_outlive_their_replays},
         {"failed_tables_do_not_step", failed_tables_do_not_step},
+        {"single_steps_of_large_contexts", single_steps_of_large_contexts},
         {"tiles_with_fluid", tiles_with_fluid},
         {"no_device_memory_beside_the_state", no_device_memory_beside_the_state},
     };
