@@ -330,7 +330,9 @@ long long lb_fluid_nodes(const lb_ctx* c);
  *    start an even number of rows apart, so that the results do not depend on it.
  *    From 12 rows on, the last rows of the last columns of each XCD's run go to
  *    short chunks (a quarter of the height, at least 4 rows) that end the step.
- *  graph_steps: time steps captured per HIP graph (even, >= 2; 0 = no graphs).
+ *  graph_steps: time steps captured per HIP graph (even, >= 2; 0 = no graphs): the
+ *    whole launches that fit (a launch of schedules 4, van der Waals, and 6 advances
+ *    2 to 6 steps, of schedule 5 two); if not one fits, none is used.
  *  fp64_arith: 0 (default) evaluates the collision in FP32; 1 evaluates its
  *    non-shear part in FP64 (schedules 3..6; schedules 0..2 then compute the
  *    whole step in FP64).  In FP32 the j/3 of the populations is formed with a

@@ -709,22 +709,41 @@ lb_status capture_graph(lb_ctx* c, int p) {
     return LB_OK;
 }
 
+// Whether a run of n steps, the last one of binary calls (call_tail) not counted,
+// replays graphs: it does from the steps of one graph on.
 bool graphs_used(const lb_ctx* c, long n) {
-    const int K = c->cfg.graph_steps;
-    return K >= 2 && (K % 2) == 0 && n >= K && c->ntiles > 0 && graph_launches(c) > 0;
+    return c->cfg.graph_steps >= 2 && c->ntiles > 0 && graph_launches(c) > 0 &&
+           n >= (long)graph_launches(c) * steps_per_launch(c);
 }
 
-// The graphs a run of n steps will replay, captured beforehand (so that the
-// capture is not inside a caller's timed region).
-lb_status prepare_graphs(lb_ctx* c, long n) {
+// Steps of a call that are launched one by one at its end (see run_steps).
+int call_tail(const lb_ctx* c, long n, bool readable) {
+    return readable && steps_per_launch(c) > 1 && c->model == LB_BINARY && n > 0 ? 1 : 0;
+}
+
+// The graphs that stepping n steps in stretches of `every` (0: in one) will replay,
+// captured beforehand (so that no capture is inside a caller's timed region).  The
+// stretches repeat after the first one, starting from either arena.
+lb_status prepare_graphs(lb_ctx* c, long n, int every) {
     if (lb_status s = check_tiled(c)) return s;
-    if (!graphs_used(c, n)) return LB_OK;
-    const int launches = graph_launches(c);
-    const int parities = (launches & 1) && n >= 2L * launches * steps_per_launch(c) ? 2 : 1;
-    for (int q = 0; q < parities; ++q) {
-        const int p = c->cur ^ q;
-        if (!c->gexec[p])
-            if (lb_status s = capture_graph(c, p)) return s;
+    const int spl = steps_per_launch(c), launches = graph_launches(c);
+    long t = c->t;
+    int cur = c->cur;
+    for (int stretch = 0; n > 0 && stretch < 3; ++stretch) {
+        const long m = every > 0 ? std::min<long>(n, every - t % every) : n;
+        n -= m;
+        t += m;
+        const int tail = call_tail(c, m, true);
+        long body = m - tail;
+        if (graphs_used(c, body)) {
+            const long replays = body / ((long)launches * spl);
+            for (int q = 0; q < ((launches & 1) && replays > 1 ? 2 : 1); ++q)
+                if (!c->gexec[cur ^ q])
+                    if (lb_status s = capture_graph(c, cur ^ q)) return s;
+            cur ^= (launches & 1) & (int)(replays & 1);
+            body -= replays * launches * spl;
+        }
+        cur ^= (int)((body + spl - 1) / spl + tail) & 1;
     }
     return LB_OK;
 }
@@ -737,8 +756,8 @@ lb_status prepare_graphs(lb_ctx* c, long n) {
 lb_status run_steps(lb_ctx* c, long n, bool readable = true) {
     if (lb_status s = check_tiled(c)) return s;
     const int spl = steps_per_launch(c);
-    const bool tail = readable && spl > 1 && c->model == LB_BINARY && n > 0;
-    if (tail) --n;
+    const int tail = call_tail(c, n, readable);
+    n -= tail;
     if (graphs_used(c, n)) {
         const int launches = graph_launches(c);
         const int K = launches * spl;
@@ -1115,7 +1134,7 @@ lb_status lb_batch_step(lb_ctx* c, long nsteps, int sample_every) {
     if (lb_status s = check_ctx(c)) return s;
     if (nsteps < 0 || sample_every < 0) return fail(LB_EINVAL, "negative step count");
     // graphs are captured before the timing events, which then bracket the launches only
-    if (lb_status s = prepare_graphs(c, sample_every > 0 ? std::min<long>(nsteps, sample_every) : nsteps)) return s;
+    if (lb_status s = prepare_graphs(c, nsteps, sample_every)) return s;
     HIP_TRY(hipEventRecord(c->ev0, c->stream));
     long left = nsteps;
     while (left > 0) {

@@ -218,6 +218,40 @@ static int single_steps_of_large_contexts() {
     return 0;
 }
 
+// A run replays graphs as soon as it holds the steps of one, and every graph of a
+// call is captured before the first launch.
+static int graphs_are_replayed() {
+    const lb_geometry large{3000, 1500, 700, 1000, 1400, 50}, mid{1024, 128, 256, 768, 40, 44};
+    for (lb_model m : {LB_VDW, LB_BINARY})
+        for (const lb_geometry& g : {SMALL, mid, large})
+            for (int graph_steps : {6, 30, 64})
+                for (int every : {0, 16, 63, 64, 65, 100}) {
+                    lb_ctx* c = context(m, {g});
+                    EXPECT(c);
+                    lb_launch_config cfg;
+                    EXPECT(lb_get_launch_config(c, &cfg) == LB_OK);
+                    cfg.graph_steps = graph_steps;
+                    EXPECT(lb_set_launch_config(c, &cfg) == LB_OK && lb_step(c, 5) == LB_OK);
+                    (void)hipStreamSynchronize(c->stream);
+                    const int K = c->block_k, held = graph_steps / K * K;   // steps of a graph
+                    EXPECT(K > 1);
+                    const HostRuntime before = rt;
+                    rt.launches.clear();
+                    EXPECT(lb_batch_step(c, 400, every) == LB_OK && lb_time(c) == 405);
+                    EXPECT(rt.late_captures == before.late_captures);
+                    long want = 0;
+                    for (long t = 5; t < 405;) {
+                        const long n = every ? std::min(405 - t, every - t % every) : 400;
+                        want += held ? (n - (m == LB_BINARY)) / held : 0;
+                        t += n;
+                    }
+                    EXPECT(rt.replays - before.replays == want);
+                    EXPECT(want > 0 ? rt.captures > before.captures : rt.captures == before.captures);
+                    lb_free(c);
+                }
+    return 0;
+}
+
 int main(int argc, char** argv) {
     const struct {
         const char* name;
@@ -226,6 +260,7 @@ int main(int argc, char** argv) {
         {"graphs_outlive_their_replays", graphs_outlive_their_replays},
         {"failed_tables_do_not_step", failed_tables_do_not_step},
         {"single_steps_of_large_contexts", single_steps_of_large_contexts},
+        {"graphs_are_replayed", graphs_are_replayed},
         {"tiles_with_fluid", tiles_with_fluid},
         {"no_device_memory_beside_the_state", no_device_memory_beside_the_state},
     };

@@ -28,6 +28,7 @@ struct HostRuntime {
     int fail_copies = 0;          // that many of the next ones fail
     std::vector<unsigned> pinned_flags, event_flags;
     int captures = 0, replays = 0;
+    int late_captures = 0;        // begun with work enqueued
     bool pending = false;         // work was enqueued and not waited for
     int destroyed_pending = 0;    // executable graphs destroyed meanwhile
     bool capturing = false;
@@ -125,6 +126,7 @@ hipError_t hipStreamSynchronize(hipStream_t) {
 }
 hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) {
     rt.capturing = true;
+    rt.late_captures += rt.pending;
     return hipSuccess;
 }
 hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) {
