@@ -353,9 +353,9 @@ lb_status lb_get_launch_config(const lb_ctx* c, lb_launch_config* cfg);
 lb_status lb_set_launch_config(lb_ctx* c, const lb_launch_config* cfg);
 
 /* Autotuner: times the candidate launch configurations on this context's own
- * lattices (each for `trial_steps` steps, state restored afterwards), keeps
- * the fastest and returns it with its time per step in microseconds.  The
- * arithmetic (fp64_arith) is not tuned: candidates keep the context's value.
+ * lattices (each for `trial_steps` steps, rounded up to whole launches; state
+ * restored afterwards), keeps the fastest and returns it with its time per step
+ * in microseconds.  The arithmetic (fp64_arith) is not tuned: candidates keep the context's value.
  * The shape found is also remembered for this process, per model and size
  * class (floor(log2) of the number of fluid nodes). */
 lb_status lb_autotune(lb_ctx* c, int trial_steps, lb_launch_config* best, double* us_per_step);

@@ -1503,16 +1503,19 @@ lb_status lb_autotune(lb_ctx* c, int trial_steps, lb_launch_config* best, double
     for (const auto& cf0 : cand) {
         lb_launch_config cf = cf0;
         if ((st = lb_set_launch_config(c, &cf))) break;
-        // (the state is restored afterwards: no read-out needs the last step single)
-        if ((st = run_steps(c, 2, false))) break;  // warm-up
+        // whole launches: one cut short takes almost a full launch's time.  (The state is
+        // restored afterwards: no read-out needs the last step single)
+        const int spl = steps_per_launch(c);
+        const long steps = ((long)trial_steps + spl - 1) / spl * spl;
+        if ((st = run_steps(c, std::max(2, spl), false))) break;  // warm-up
         if (!hip_ok(hipEventRecord(c->ev0, c->stream), "hipEventRecord")) break;
-        if ((st = run_steps(c, trial_steps, false))) break;
+        if ((st = run_steps(c, steps, false))) break;
         float ms = 0.f;
         if (!hip_ok(hipEventRecord(c->ev1, c->stream), "hipEventRecord") ||
             !hip_ok(hipEventSynchronize(c->ev1), "hipEventSynchronize") ||
             !hip_ok(hipEventElapsedTime(&ms, c->ev0, c->ev1), "hipEventElapsedTime"))
             break;
-        const double us = 1000.0 * ms / trial_steps;
+        const double us = 1000.0 * ms / steps;
         if (us < best_us) {
             best_us = us;
             best_cfg = cf;

@@ -252,6 +252,32 @@ static int graphs_are_replayed() {
     return 0;
 }
 
+// The tuner times whole launches only, at least trial_steps steps of each candidate.
+static int tuner_times_whole_launches() {
+    const lb_geometry mid{1024, 128, 256, 768, 40, 44}, wide{2600, 560, 500, 1900, 440, 50};
+    for (lb_model m : {LB_VDW, LB_BINARY})
+        for (const lb_geometry& g : {SMALL, mid, wide})
+            for (int trial : {2, 3, 5, 10, 128}) {
+                lb_ctx* c = context(m, {g});
+                EXPECT(c);
+                const int K = c->block_k;
+                rt.launches.clear();
+                lb_launch_config best;
+                double us;
+                EXPECT(lb_autotune(c, trial, &best, &us) == LB_OK && lb_time(c) == 0);
+                int steps = 0;
+                for (const Launched& l : rt.launches)
+                    if (l.kernel.find("lb_block") != std::string::npos) {
+                        EXPECT(l.block.steps == K && l.block.halo == 2 * K);
+                        steps += l.block.steps;
+                    }
+                EXPECT(steps >= trial + 2);
+                if (m == LB_VDW) EXPECT(rt.count("lb_wide_vdw") == 0);   // (an odd step of schedule 5)
+                lb_free(c);
+            }
+    return 0;
+}
+
 int main(int argc, char** argv) {
     const struct {
         const char* name;
@@ -261,6 +287,7 @@ int main(int argc, char** argv) {
         {"failed_tables_do_not_step", failed_tables_do_not_step},
         {"single_steps_of_large_contexts", single_steps_of_large_contexts},
         {"graphs_are_replayed", graphs_are_replayed},
+        {"tuner_times_whole_launches", tuner_times_whole_launches},
         {"tiles_with_fluid", tiles_with_fluid},
         {"no_device_memory_beside_the_state", no_device_memory_beside_the_state},
     };
