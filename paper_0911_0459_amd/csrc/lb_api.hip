@@ -949,8 +949,9 @@ lb_status moments_into(lb_ctx* c, int k, long long k0, long long k1, float* rho,
 // us, now 25) and staged fields through a vector (lb_batch_moments of 512 x 64 nodes:
 // 160 us, now 80).
 lb_status ensure_pin(lb_ctx* c) {
+    // (the host reads one half while kernels that fill the other one are still enqueued)
     for (hipEvent_t& e : c->pin_ev)
-        if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        if (!e) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming | hipEventReleaseToSystem));
     if (!c->pin) c->pin = pin_take();
     return c->pin ? LB_OK : fail(LB_ENOMEM, "allocation of pinned host memory failed");
 }
@@ -1076,7 +1077,8 @@ char* lbk::pin_take() {
         }
     }
     void* p = nullptr;
-    return hipHostMalloc(&p, PIN_BYTES, hipHostMallocPortable) == hipSuccess ? (char*)p : nullptr;
+    const unsigned flags = hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent;
+    return hipHostMalloc(&p, PIN_BYTES, flags) == hipSuccess ? (char*)p : nullptr;
 }
 
 void lbk::pin_give(char* p) {

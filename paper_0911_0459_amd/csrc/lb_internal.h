@@ -12,7 +12,8 @@ namespace lbk {
 lb_status set_error(lb_status s, const char* msg);
 
 // Pinned host memory that the kernels of read-outs write (and mlp_predict's reads)
-// themselves, PIN_BYTES a piece.  An object takes a piece with its first read-out and
+// themselves, PIN_BYTES a piece; coherent by its flags, whatever the environment makes
+// the default.  An object takes a piece with its first read-out and
 // gives it back when it is freed, with its stream drained; up to PIN_KEPT pieces wait
 // for the next object (allocating one takes about 130 us), more are freed.
 // pin_take returns null if the allocation fails.

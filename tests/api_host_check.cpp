@@ -278,6 +278,24 @@ static int tuner_times_whole_launches() {
     return 0;
 }
 
+// Read-outs pass through memory that is coherent by its flags, and the events that the
+// host waits for in between release to the system.
+static int read_outs_are_coherent() {
+    lb_ctx* c = context(LB_BINARY, {SMALL});
+    EXPECT(c);
+    rt.event_flags.clear();
+    std::vector<double> q((size_t)SMALL.nx * SMALL.ny);
+    EXPECT(lb_moments(c, q.data(), nullptr, nullptr, nullptr) == LB_OK);
+    int n = 0;
+    EXPECT(lb_batch_l_history(c, 0, nullptr, nullptr, 0, &n) == LB_OK);
+    EXPECT(rt.pinned_flags.size() == 1 && rt.event_flags.size() == 2);
+    EXPECT((rt.pinned_flags[0] & hipHostMallocCoherent) && (rt.pinned_flags[0] & hipHostMallocMapped) &&
+           (rt.pinned_flags[0] & hipHostMallocPortable) && !(rt.pinned_flags[0] & hipHostMallocNonCoherent));
+    for (unsigned f : rt.event_flags) EXPECT((f & hipEventReleaseToSystem) && (f & hipEventDisableTiming));
+    lb_free(c);
+    return 0;
+}
+
 int main(int argc, char** argv) {
     const struct {
         const char* name;
@@ -288,6 +306,7 @@ int main(int argc, char** argv) {
         {"single_steps_of_large_contexts", single_steps_of_large_contexts},
         {"graphs_are_replayed", graphs_are_replayed},
         {"tuner_times_whole_launches", tuner_times_whole_launches},
+        {"read_outs_are_coherent", read_outs_are_coherent},
         {"tiles_with_fluid", tiles_with_fluid},
         {"no_device_memory_beside_the_state", no_device_memory_beside_the_state},
     };
