@@ -350,6 +350,10 @@ typedef struct {
 } lb_launch_config;
 
 lb_status lb_get_launch_config(const lb_ctx* c, lb_launch_config* cfg);
+/* Time steps that a launch advances under the current configuration (schedule 5: 2;
+ * the tiles of schedules 4, van der Waals, and 6: as planned for the active
+ * capillaries; else 1).  0 for a null context. */
+int lb_steps_per_launch(const lb_ctx* c);
 lb_status lb_set_launch_config(lb_ctx* c, const lb_launch_config* cfg);
 
 /* Autotuner: times the candidate launch configurations on this context's own

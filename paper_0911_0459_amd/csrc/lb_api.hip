@@ -1420,6 +1420,8 @@ lb_status lb_get_launch_config(const lb_ctx* c, lb_launch_config* cfg) {
     return LB_OK;
 }
 
+int lb_steps_per_launch(const lb_ctx* c) { return c ? steps_per_launch(c) : 0; }
+
 lb_status lb_set_launch_config(lb_ctx* c, const lb_launch_config* cfg) {
     if (!c || !cfg) return fail(LB_EINVAL, "null argument");
     const int r = cfg->tile_rows;

@@ -85,6 +85,7 @@ _SIGS = {
     "lb_batch_health": (C.c_int, [_vp, _ip]),
     "lb_batch_size": (C.c_int, [_vp]),
     "lb_fluid_nodes": (C.c_longlong, [_vp]),
+    "lb_steps_per_launch": (C.c_int, [_vp]),
     "lb_get_launch_config": (C.c_int, [_vp, C.POINTER(lb_launch_config)]),
     "lb_set_launch_config": (C.c_int, [_vp, C.POINTER(lb_launch_config)]),
     "lb_autotune": (C.c_int, [_vp, C.c_int, C.POINTER(lb_launch_config), _dp]),
@@ -362,6 +363,10 @@ class Lattice:
         return int(_lib.lb_fluid_nodes(self._h))
 
     # -- launch configuration ----------------------------------------------------
+    @property
+    def steps_per_launch(self) -> int:
+        return int(_lib.lb_steps_per_launch(self._h))
+
     def launch_config(self) -> lb_launch_config:
         cfg = lb_launch_config()
         _check(_lib.lb_get_launch_config(self._h, C.byref(cfg)))
