@@ -1,5 +1,6 @@
 // Checks of the block kernels' planning on the host.
 #include <cstdio>
+#include <cstdlib>
 #include <vector>
 
 #include "lb_block_table.h"
@@ -44,4 +45,19 @@ static int kept_counts() {
     return 0;
 }
 
-int main() { return kept_counts(); }
+// `model nx ny x_in tube_len tube_h y0`: the plan of that lattice and the tiles of the
+// column in the middle of its tube.
+static int print_plan(char** v) {
+    const bool vdw = v[1][0] == 'v';
+    const lb_geometry g{std::atoi(v[2]), std::atoi(v[3]), std::atoi(v[4]), std::atoi(v[5]), std::atoi(v[6]), std::atoi(v[7])};
+    const BlockPlan p = plan_block_tiles(std::vector<lb_geometry>{g}, {1}, vdw);
+    std::vector<BlockDev> t;
+    build_blocks({g}, {1}, p.K, block_rx(p.shape), block_ry(p.shape, vdw), block_align(p.shape, vdw), &t);
+    int column = 0;
+    const int x = g.x_in + g.tube_len / 2;
+    for (const BlockDev& b : t) column += b.xs <= x && x < b.xe;
+    std::printf("%d %d %d\n", p.shape, p.K, column);
+    return 0;
+}
+
+int main(int argc, char** argv) { return argc == 8 ? print_plan(argv) : kept_counts(); }

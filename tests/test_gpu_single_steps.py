@@ -43,3 +43,28 @@ def test_rows_and_tiles_step_alike(L, model, fp64, force):
     for other in out[1:]:
         for x, y in zip(out[0], other):
             assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("chunk", [0, 4, 5, 12, 16])
+@pytest.mark.parametrize("model", list(GEOMS))
+def test_row_sweep_of_single_steps_does_not_depend_on_the_chunking(L, model, chunk):
+    """The row sweep behind the single steps takes its chunks from the launch
+    configuration; with van der Waals it also ends odd calls of schedule 5."""
+    g = GEOMS[model]
+    vdw = model == "vdw"
+    kw = dict(I.VDW_CONSTS, nu_l=0.13, wall_grad=-0.1) if vdw else dict(I.BIN_CONSTS, nu_l=0.4, nu_g=0.1, wall_grad=-0.2)
+    q = np.where(np.arange(g[0]) < 0.45 * g[0], *((4.5, 2.6) if vdw else (1.0, -1.0))) + np.zeros((g[1], 1))
+    out = []
+    for cfg, calls in ((dict(), [5]), (dict(chunk_rows=chunk), [1] * 5), (dict(schedule=5, chunk_rows=chunk), [1, 3, 1])):
+        if cfg.get("schedule") == 5 and not vdw:
+            continue
+        print(f"chunks {model} {cfg} {calls}", flush=True)
+        lat = L.Lattice(L.make_params(model, **kw), L.make_geometry(*g), q)
+        lat.set_launch_config(**dict(lat.launch_config().asdict(), **cfg))
+        for n in calls:
+            lat.step(n)
+        out.append(lat.moments())
+        lat.close()
+    for other in out[1:]:
+        for x, y in zip(out[0], other):
+            assert np.array_equal(x, y)
