@@ -56,7 +56,7 @@ def moved_bytes_per_lup(model: str, schedule: int, steps_per_launch: int) -> flo
 
 
 # the step kernels and the strip table that shapes their traffic
-KERNEL_SOURCES = ("lb_internal.h", "lb_kernels.h", "lb_strip.h", "lb_strip_table.h", "lb_wide.h", "lb_wide2.h", "lb_wmom.h",
+KERNEL_SOURCES = ("lb_barrier.h", "lb_internal.h", "lb_kernels.h", "lb_strip.h", "lb_strip_table.h", "lb_wide.h", "lb_wide2.h", "lb_wmom.h",
                   "lb_block.h", "lb_block_table.h")
 
 

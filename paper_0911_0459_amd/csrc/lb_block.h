@@ -46,6 +46,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "lb_barrier.h"
 #include "lb_block_table.h"
 #include "lb_wmom.h"
 

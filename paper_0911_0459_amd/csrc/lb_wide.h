@@ -23,6 +23,7 @@
 // next row's slots while the others still read the current ones.  The
 // population loads requested one row ahead stay in flight across the barriers.
 #pragma once
+#include "lb_barrier.h"
 #include "lb_strip.h"
 
 namespace lbk {
@@ -32,14 +33,6 @@ constexpr int NWM = WIDE_OUT / SW;             // main wavefronts
 constexpr int WIDE_THREADS = (NWM + 1) * SW;   // main wavefronts and the halo wavefront
 constexpr int WU = WIDE_OUT + 2;               // u / mu row: columns xs-1 .. xs+WIDE_OUT
 constexpr int WP = WIDE_OUT + 4;               // phi row: columns xs-2 .. xs+WIDE_OUT+1
-
-// Workgroup barrier that orders LDS accesses only.  __syncthreads() would also
-// wait for every outstanding global load, including the row requested ahead.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 
 // Role of a thread of a wide strip.
 struct WideLane {

@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "lbcap.h"
+#include "lb_barrier.h"
 #include "lb_internal.h"
 
 namespace {
@@ -98,13 +99,9 @@ struct RowsArgs {
     float* loss;            // sum of squared errors, one per workgroup
 };
 
-// Workgroup barrier that orders LDS accesses only: the weights requested ahead stay
-// in flight, and nothing that the kernel stores is read by it.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
+// (the weights requested ahead stay in flight over it, and nothing that a kernel of
+// this file stores is read by the same kernel)
+using lbk::lds_barrier;
 
 // The stream of weights of one wavefront: chunks of 16 k x 64 columns, four 16-byte
 // words per lane, through the four layers and (gradient) back through the last
