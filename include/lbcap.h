@@ -123,7 +123,10 @@ lb_status lb_init(lb_ctx** out, const lb_params* p, const lb_geometry* g, const 
  * nodes.  Asynchronous; errors of the launches are reported here, a numerical
  * blow-up by lb_check or the next call that reads data back.  LB_ESTATE if the
  * last call that sets what is launched (a launch configuration, retire, revive,
- * lb_load) failed on the device: repeating that call mends it. */
+ * lb_load) failed on the device: repeating that call mends it.
+ * On a stream that the caller captures, an even number of steps below graph_steps
+ * (any, with graph_steps 0) is recorded so that every replay advances the lattice by
+ * it (lb_time counts the call, not the replays); more are refused (LB_EDEVICE). */
 lb_status lb_step(lb_ctx* c, long nsteps);
 
 /* Number of steps taken since lb_init / lb_load. */

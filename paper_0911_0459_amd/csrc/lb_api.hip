@@ -724,8 +724,13 @@ int call_tail(const lb_ctx* c, long n, bool readable) {
 // The graphs that stepping n steps in stretches of `every` (0: in one) will replay,
 // captured beforehand (so that no capture is inside a caller's timed region).  The
 // stretches repeat after the first one, starting from either arena.
-lb_status prepare_graphs(lb_ctx* c, long n, int every) {
+lb_status prepare_graphs(lb_ctx* c, long n, int every, bool captured) {
     if (lb_status s = check_tiled(c)) return s;
+    if (captured) {
+        if (c->cfg.graph_steps >= 2 && (every > 0 ? std::min<long>(n, every) : n) >= c->cfg.graph_steps)
+            return fail(LB_EDEVICE, "a captured call steps less than graph_steps at a time (0: any number)");
+        return LB_OK;
+    }
     const int spl = steps_per_launch(c), launches = graph_launches(c);
     long t = c->t;
     int cur = c->cur;
@@ -753,12 +758,15 @@ lb_status prepare_graphs(lb_ctx* c, long n, int every) {
 // phi of the state's own time, after a launch of several steps the phi of an
 // earlier one (those in between stay in LDS).  With several steps per launch the
 // binary model's last step is therefore a launch of its own.
-lb_status run_steps(lb_ctx* c, long n, bool readable = true) {
+// captured: the caller captures the stream.  No graph is replayed into his, and there
+// are evenly many launches for an even number of steps, whatever a launch advances: a
+// replay then leaves the state in the arena that the next replay reads.
+lb_status run_steps(lb_ctx* c, long n, bool readable = true, bool captured = false) {
     if (lb_status s = check_tiled(c)) return s;
     const int spl = steps_per_launch(c);
     const int tail = call_tail(c, n, readable);
     n -= tail;
-    if (graphs_used(c, n)) {
+    if (!captured && graphs_used(c, n)) {
         const int launches = graph_launches(c);
         const int K = launches * spl;
         while (n >= K) {
@@ -775,6 +783,12 @@ lb_status run_steps(lb_ctx* c, long n, bool readable = true) {
         c->cur ^= 1;
         c->t += steps;
     };
+    if (captured && (((n + spl - 1) / spl + n) & 1)) {   // one launch more: the first one in two
+        const int first = (int)std::min<long>(n, spl);
+        launch(1);
+        launch(first - 1);
+        n -= first;
+    }
     for (; n > 0; n -= std::min<long>(n, spl)) launch((int)std::min<long>(n, spl));
     if (tail) launch(1);
     HIP_TRY(hipGetLastError());
@@ -1135,14 +1149,16 @@ lb_status lb_step(lb_ctx* c, long nsteps) { return lb_batch_step(c, nsteps, 0); 
 lb_status lb_batch_step(lb_ctx* c, long nsteps, int sample_every) {
     if (lb_status s = check_ctx(c)) return s;
     if (nsteps < 0 || sample_every < 0) return fail(LB_EINVAL, "negative step count");
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    const bool captured = hipStreamIsCapturing(c->stream, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone;
     // graphs are captured before the timing events, which then bracket the launches only
-    if (lb_status s = prepare_graphs(c, nsteps, sample_every)) return s;
+    if (lb_status s = prepare_graphs(c, nsteps, sample_every, captured)) return s;
     HIP_TRY(hipEventRecord(c->ev0, c->stream));
     long left = nsteps;
     while (left > 0) {
         long chunk = left;
         if (sample_every > 0) chunk = std::min(left, sample_every - (c->t % sample_every));
-        lb_status s = run_steps(c, chunk);
+        lb_status s = run_steps(c, chunk, true, captured);
         if (s) return s;
         left -= chunk;
         if (sample_every > 0 && c->t % sample_every == 0) {

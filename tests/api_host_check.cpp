@@ -296,6 +296,52 @@ static int read_outs_are_coherent() {
     return 0;
 }
 
+// Under a caller's capture a call is direct launches, evenly many for an even number
+// of steps; one that steps graph_steps at a time is refused.
+static int captured_calls_can_be_replayed() {
+    const lb_geometry mid{1024, 128, 256, 768, 40, 44}, large{3000, 1500, 700, 1000, 1400, 50};
+    for (lb_model m : {LB_VDW, LB_BINARY})
+        for (const lb_geometry& g : {SMALL, mid, large})
+            for (int schedule : {m == LB_VDW ? 4 : 6, 3, 5})
+                for (int every : {0, 7})
+                    for (long n = 1; n < 70; ++n) {
+                        static lb_ctx* c = nullptr;
+                        static lb_launch_config cfg;
+                        if (n == 1) {
+                            lb_free(c);
+                            c = context(m, {g});
+                            EXPECT(c && lb_get_launch_config(c, &cfg) == LB_OK);
+                            cfg.schedule = schedule;
+                            EXPECT(lb_set_launch_config(c, &cfg) == LB_OK);
+                            EXPECT(lb_step(c, 200) == LB_OK);   // (its graphs are there)
+                        }
+                        const long t = lb_time(c);
+                        const int cur = c->cur, replays = rt.replays;
+                        hipGraph_t graph;
+                        EXPECT(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal) == hipSuccess);
+                        rt.launches.clear();
+                        const lb_status s = lb_batch_step(c, n, every);
+                        EXPECT(rt.capturing && rt.replays == replays);
+                        EXPECT(hipStreamEndCapture(c->stream, &graph) == hipSuccess && hipGraphDestroy(graph) == hipSuccess);
+                        if (!every && n >= cfg.graph_steps) {
+                            EXPECT(s == LB_EDEVICE && rt.launches.empty() && lb_time(c) == t);
+                            continue;
+                        }
+                        EXPECT(s == LB_OK && lb_time(c) == t + n);
+                        int steps = 0, launches = 0;
+                        for (const Launched& l : rt.launches) {
+                            if (l.kernel.find("lb_interface") != std::string::npos ||
+                                l.kernel.find("lb_health") != std::string::npos)
+                                continue;
+                            ++launches;
+                            const bool two = l.kernel.find("lb_wide2") != std::string::npos;
+                            steps += l.kernel.find("lb_block") != std::string::npos ? l.block.steps : 1 + two;
+                        }
+                        EXPECT(steps == n && launches % 2 == n % 2 && (c->cur ^ cur) == n % 2);
+                    }
+    return 0;
+}
+
 int main(int argc, char** argv) {
     const struct {
         const char* name;
@@ -307,6 +353,7 @@ int main(int argc, char** argv) {
         {"graphs_are_replayed", graphs_are_replayed},
         {"tuner_times_whole_launches", tuner_times_whole_launches},
         {"read_outs_are_coherent", read_outs_are_coherent},
+        {"captured_calls_can_be_replayed", captured_calls_can_be_replayed},
         {"tiles_with_fluid", tiles_with_fluid},
         {"no_device_memory_beside_the_state", no_device_memory_beside_the_state},
     };

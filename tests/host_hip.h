@@ -125,8 +125,13 @@ hipError_t hipStreamSynchronize(hipStream_t) {
     return hipSuccess;
 }
 hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) {
+    if (rt.capturing) return hipErrorIllegalState;
     rt.capturing = true;
     rt.late_captures += rt.pending;
+    return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) {
+    *s = rt.capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return hipSuccess;
 }
 hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) {
