@@ -79,7 +79,7 @@ __global__ void __launch_bounds__(256) mlp_pack(const float* __restrict__ P, flo
 // What mlp_rows leaves for mlp_wgrad, in the order in which that kernel's lanes
 // multiply: rows in groups of 16, columns in tiles of 16, and per group and tile
 // [row % 4][column % 16][row / 4 % 4].  Rows past the last one of the pass up to a
-// multiple of 16 are zero in the output gradients and finite in the activations.
+// multiple of 16 are zero.
 __device__ __forceinline__ long grad_at(int ntile, int group, int tile, int r4, int c) {
     return ((long)(group * ntile + tile) * 64 + r4 * 16 + c) * 4;
 }
@@ -238,7 +238,13 @@ __global__ void __launch_bounds__(256, GRAD && MT == 2 ? 2 : 1) mlp_rows(RowsArg
                 const float z = acc[m][v] + bias;
                 const float e1 = gelu_e1(z);
                 h[m][v] = gelu(z, e1);
-                if (GRAD) gp[l][m][v] = gelu_grad(z, e1);
+                if (GRAD) {
+                    // a row past the last one ends here, or its biases alone could take it
+                    // to an infinity, which times its zero gradient is no zero
+                    const bool row = r0 + 4 * m + v < a.n;
+                    h[m][v] = row ? h[m][v] : 0.f;
+                    gp[l][m][v] = row ? gelu_grad(z, e1) : 0.f;
+                }
             }
             *(f4*)&Hb[cur ^ 1][(m * WMAX + col) * 4] = h[m];
         }
