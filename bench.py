@@ -111,8 +111,8 @@ def step_kernel(model: str, cfg: dict) -> str:
 def roofline(model: str, cfg: dict, workload: str, fluid: int, us: float, steps_per_launch: int, copy_gbps: float):
     """The step kernel against HBM, everything per time step: `achieved` is the
     method's algorithmic bytes over the time, `traffic` the measured bytes (a
-    launch's, from the counter summaries, over its steps).  The tile kernels keep
-    the vector ALU busy (85 - 95 % by its counters), so memory is not their bound."""
+    launch's, from the counter summaries, over its steps).  The tile kernels
+    saturate the vector ALU (by its counters), so memory is not their bound."""
     kernel = step_kernel(model, cfg)
     per_launch = traffic_from_profiles(kernel, workload, cfg)
     bpl = BYTES_PER_LUP[model]
@@ -241,7 +241,7 @@ def oracle_next_to_gpu(L, log):
         t_cpu = time.perf_counter() - t0
         lat = L.Lattice(L.params_from_workload(w), L.geometry_from_workload(w), w.initial_field())
         lat.autotune(trial_steps=10)
-        lat.step(50)
+        lat.step(200)   # (its graphs, of up to 64 steps, are captured)
         lat.check()
         torch.cuda.synchronize()
         t0 = time.perf_counter()

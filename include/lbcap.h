@@ -292,33 +292,35 @@ long long lb_fluid_nodes(const lb_ctx* c);
  *    output columns marching along y through chunks of chunk_rows rows (0: the
  *    whole height), strips grouped so that each of the 8 XCDs works on a
  *    contiguous run of them; every population row is read once per step.
- *    4 binary model: the same row sweep with a workgroup per strip of 192 output columns
- *    aligned to the row pitch (three wavefronts of 64 output columns and one
- *    that supplies the two neighbour columns), so that no stored cache line is
+ *    4 binary model: the same row sweep with a workgroup per strip of 192 output
+ *    columns aligned to the row pitch (three wavefronts of 64 output columns and
+ *    one that supplies the two neighbour columns), so that no stored cache line is
  *    shared between workgroups.  The same arithmetic as 3, compiled apart:
  *    the results agree within 3e-7.  Van der Waals model (its default): several
  *    steps per launch in tiles whose steps run in LDS, cut for the context's
- *    lattices (no chunks); results bitwise those of 3, however steps are grouped.
+ *    lattices; single steps of contexts of 1.5 million active fluid nodes and more
+ *    by the wide strips.  Results bitwise those of 3, however steps are grouped.
  *    5 the strips of 4 (either model), each launch advancing two time steps: the sweep
  *    reads the populations (and phi) once with a halo of three nodes (binary
  *    model: four), keeps the intermediate step in LDS and writes the second
  *    step, so that the populations cross HBM once per two steps; an odd step
- *    count ends with one launch of schedule 4, and with the binary model every
- *    stepping call does (the read-outs take phi of the step the last launch
+ *    count ends with one single step of the wide strips, and with the binary model
+ *    every stepping call does (the read-outs take phi of the step the last launch
  *    read, which a two-step launch leaves one step behind).  The same
  *    arithmetic per step as schedule 4 (the intermediate step rounded to
  *    FP32, phi to its fixed point, as a single step stores them): van der
  *    Waals results are bitwise those of schedules 3 and 4, binary ones agree to
  *    rounding.
  *    6 (binary model only; its default) several steps per launch in tiles whose
- *    steps run in LDS, cut for the context's lattices (no chunks), over a stored
- *    state of seven FP32
- *    planes instead of nine populations: with the rates of Appendix A the
+ *    steps run in LDS, cut for the context's lattices, over a stored state of seven
+ *    FP32 planes instead of nine populations: with the rates of Appendix A the
  *    post-collision populations of a node follow from rho - rho_ref, j* / 3, the
  *    common parts of the axis and of the diagonal populations, pxx* and pxy*,
  *    so a node is 32 instead of 40 bytes (phi included).  Every stepping call
- *    ends with a launch of one step (as with 5); the results do not depend on
- *    how steps are grouped into calls or launches.
+ *    ends with a single step (as with 5), which costs a large context more than a
+ *    step of a full launch: long calls are cheaper.  Single steps of contexts of 4
+ *    million active fluid nodes and more go by wide strips over the same storage.
+ *    The results do not depend on how steps are grouped into calls or launches.
  *    Setting this schedule converts the stored state in place
  *    (both buffers); leaving it converts back (a context of the binary model
  *    starts in it).  Results agree with schedule 4
@@ -328,9 +330,11 @@ long long lb_fluid_nodes(const lb_ctx* c);
  *    halo: 0 one workgroup per tile in table order, 1 tiles grouped per XCD,
  *    2 persistent workgroups (persist_blocks_per_cu x 256 CUs) striding the table.
  *  tile_rows: rows per tile for schedules 0..2 (1, 2, 4 or 8).
- *  chunk_rows: target rows per strip chunk for the row sweeps of schedules 3..5 (0, or 4..4096,
- *    checked for every schedule; default 8 for the van der Waals model, 20 for the binary one): each strip column is cut into chunks of about that height that
- *    start an even number of rows apart, so that the results do not depend on it.
+ *  chunk_rows: target rows per strip chunk of the row sweeps (schedules 3..5, and the
+ *    single steps of large contexts in 4 and 6; 0, or 4..4096; default 8 for the van
+ *    der Waals model, 20 for the binary one): each strip column is cut into chunks of
+ *    about that height that start an even number of rows apart, so that the results
+ *    do not depend on it.
  *    From 12 rows on, the last rows of the last columns of each XCD's run go to
  *    short chunks (a quarter of the height, at least 4 rows) that end the step.
  *  graph_steps: time steps captured per HIP graph (even, >= 2; 0 = no graphs): the

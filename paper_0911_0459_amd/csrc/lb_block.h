@@ -22,16 +22,16 @@
 // written in the second one, so it has two.
 //
 // What bounds it.  A small lattice is a chain of latencies: one node's arithmetic
-// and two barriers (1.1 us a step for van der Waals, 1.8 us for the binary model)
-// and a K-th of 3.5 us for the launch, the loads and the stores.  The row sweeps,
-// marching a few dozen workgroups through their rows at about 2 us a row, left most
-// CUs idle: vdW 256 x 64 10.1 -> 1.6 us per step, binary 1024 x 128 46.2 -> 2.7 us,
-// binary 4096 x 256 47.1 -> 8.9 us.  A large one is bound by the vector ALU (vdW
-// 16384 x 1024 at K = 4: 45 M wavefront instructions a step, all its cycles; the
-// 256-capillary sweep: 80 % of them; halo nodes are a third to a half of the work):
-// with K = 2 a node's state crosses HBM once per two steps instead of every step, and
-// the sweep runs at 345 instead of 495 us per step.  On vdW 16384 x 1024 K = 4
-// measured 68.5 us (K = 3: 79, K = 2: 103; two steps per row sweep, schedule 5: 102).
+// and two barriers (1.0 us a step for van der Waals, 1.5 us for the binary model)
+// and a K-th of 2.6 us for the launch, the loads and the stores (the fits of
+// lb_block_table.h, 24-row shape).  The row sweeps, marching a few dozen workgroups
+// through their rows at about 2 us a row, left most CUs idle: vdW 256 x 64 10.1 -> 1.5
+// us per step, binary 1024 x 128 46.2 -> 2.5 us, binary 4096 x 256 47.1 -> 8.4 us.  A
+// large one is bound by the vector ALU, all its cycles (vdW 16384 x 1024 at K = 4: 157 M
+// wavefront instructions a launch; the 256-capillary sweep at K = 3: 631 M; halo nodes
+// are a third to a half of the work): the state crosses HBM once per launch instead of
+// every step, and the sweep runs at 346 instead of 495 us per step.  On vdW 16384 x 1024
+// K = 4 measured 68 us (K = 3: 79, K = 2: 103; two steps per row sweep, schedule 5: 96).
 // Two nodes per thread in the 64-column shape: one row per wavefront (scalar row
 // data, no lane masks for the rows) and both nodes' neighbours at constant distances
 // from two address registers keep it to 80 (binary) and 58 registers, two workgroups
@@ -39,7 +39,8 @@
 //
 // Every wavefront of a workgroup waits for the one at the wall, so its ghosts and
 // bounce-back sources are picked among values already read instead of read under a
-// branch for each direction (the sweep 382 -> 345 us, binary 1024 x 128 3.3 -> 2.7 us),
+// branch for each direction (the sweep 382 -> 345 us, binary 1024 x 128 3.3 -> 2.7 us
+// at that step),
 // and wavefronts without solid neighbours run code compiled for none (vdW
 // 16384 x 1024 70.7 -> 68.6 us).
 #pragma once

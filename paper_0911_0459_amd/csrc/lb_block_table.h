@@ -91,8 +91,9 @@ inline int block_rx(int shape) { return shape == 1 ? 64 : 32; }
 inline int block_ry(int shape, bool vdw) { return shape == 2 || (shape == 1 && !vdw) ? 24 : 32; }
 // Columns the tiles are cut at.  A lattice beyond the caches is bound by the lines
 // its tiles share: whole 64-byte sectors measured 71.9 against 74.0 us per step
-// (vdW 16384 x 1024, K = 4).  The binary tiles (K = 2: 56 columns) would lose more
-// columns than that gains (the 256-capillary sweep: 422 against 374 us).
+// (vdW 16384 x 1024, K = 4).  The binary tiles (52 columns at K = 3, 56 at K = 2) would
+// lose more columns, down to 48, than that gains (the 256-capillary sweep: 422 against
+// 374 us).
 inline int block_align(int shape, bool vdw) { return shape == 1 && vdw ? 16 : 1; }
 
 // What a launch of shape `shape` costs at K steps, kmin <= K <= kmax (see plan_block_tiles).
@@ -143,7 +144,7 @@ inline size_t block_capacity(const std::vector<BlockCounts>& counts) {
 // nodes (binary 8192 x 1024: 79 against 102 us).
 //
 // counts: count_blocks of each capillary, kept by the caller, who plans again whenever
-// one retires (counting all plans of 256 capillaries takes the host 3 ms, summing 10 us).
+// one retires (counting all plans of 256 capillaries takes the host 1 to 3 ms, summing them 1 us).
 inline BlockPlan plan_block_tiles(const std::vector<BlockCounts>& counts, const std::vector<int>& active, bool vdw) {
     std::array<size_t, BLOCK_PLANS> total{};
     for (size_t k = 0; k < counts.size(); ++k)

@@ -1,5 +1,6 @@
 """The roofline entry of bench.py (no GPU): every figure is per time step, whatever a
 launch advances."""
+import json
 import os
 import sys
 
@@ -37,3 +38,16 @@ def test_figures_are_per_step(monkeypatch, model, schedule, steps, kernel, bound
 def test_no_traffic_without_a_summary(monkeypatch):
     monkeypatch.setattr(bench, "traffic_from_profiles", lambda *a: None)
     assert bench.roofline("binary", dict(CFG, schedule=6), "sweep", 1, 0.0, 3, 6000.0)["traffic"] is None
+
+
+@pytest.mark.parametrize("name,schedule,steps,lo,hi", [("lb_block_bin_sweep_counters.json", 6, 3, 0.25, 0.35),
+                                                       ("lb_block_vdw_vdw16k_counters.json", 4, 4, 0.3, 0.45)])
+def test_committed_summaries_of_the_tile_kernels(name, schedule, steps, lo, hi):
+    """Their launch shape and steps per launch, every command a rocprofv3 call of
+    committed files, and a launch that moves a fraction of its steps' algorithmic
+    bytes (a third and a quarter, and the halos)."""
+    d = json.load(open(os.path.join(ROOT, "profiles", name)))
+    assert d["launch"]["schedule"] == schedule and d["steps_per_launch"] == steps
+    assert d["kernel"].startswith(bench.step_kernel("binary" if schedule == 6 else "vdw", d["launch"]))
+    assert lo < d["hbm_bytes_per_launch"] / d["algorithmic_bytes_per_launch"] < hi
+    assert all(c.startswith(("cd ", "rocprofv3 ")) for c in d["commands"])
