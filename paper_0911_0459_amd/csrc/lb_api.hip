@@ -264,7 +264,7 @@ lb_status make_layout(int n, const lb_params* P, const lb_geometry* G, Layout& L
         const std::vector<lb_geometry> gv(G, G + n);
         L.max_strips = std::max(strip_capacity(gv, STRIP_OUT), strip_capacity(gv, WIDE_OUT));
         for (const lb_geometry& g : gv) L.blocks.push_back(count_blocks(g, P[0].model == LB_VDW));
-        L.max_blocks = block_capacity(L.blocks);
+        L.max_blocks = block_capacity(L.blocks, P[0].model == LB_VDW);
         if (L.max_blocks > 0x7ffffff0u) return fail(LB_EINVAL, "tile table too large");
     }
     size_t o = 0;
@@ -451,7 +451,7 @@ bool rows_for_single_steps(const lb_ctx* c) {
 lb_status upload_blocks(lb_ctx* c) {
     std::vector<BlockDev>& t = c->h_blocks;
     const bool vdw = c->model == LB_VDW;
-    const BlockPlan p = plan_block_tiles(c->L.blocks, c->active, vdw);
+    const BlockPlan p = plan_block_tiles(c->L.blocks, c->active, vdw, c->L.max_blocks);
     if (p.tiles == 0) return LB_OK;   // every capillary is retired
     t.reserve(p.tiles);
     build_blocks(c->G, c->active, p.K, block_rx(p.shape), block_ry(p.shape, vdw), block_align(p.shape, vdw), &t);

@@ -3,6 +3,7 @@
 #pragma once
 #include <algorithm>
 #include <array>
+#include <cstdint>
 #include <vector>
 
 #include "lbcap.h"
@@ -123,14 +124,6 @@ inline BlockCounts count_blocks(const lb_geometry& g, bool vdw) {
     return n;
 }
 
-// Tiles that a table may need, whatever the plan and the set of active capillaries:
-// the most that any plan cuts each capillary into.
-inline size_t block_capacity(const std::vector<BlockCounts>& counts) {
-    size_t total = 0;
-    for (const BlockCounts& n : counts) total += *std::max_element(n.begin(), n.end());
-    return total;
-}
-
 // The cheapest plan.  A launch costs its own latency, which grows with K, and so much
 // for every further tile of a CU: whole rounds of 256 tiles up to the second (the 5 x
 // 512 x 64 batch of the binary model: 250 tiles at K = 3 3.05 us a step, 290 at K = 4
@@ -145,7 +138,9 @@ inline size_t block_capacity(const std::vector<BlockCounts>& counts) {
 //
 // counts: count_blocks of each capillary, kept by the caller, who plans again whenever
 // one retires (counting all plans of 256 capillaries takes the host 1 to 3 ms, summing them 1 us).
-inline BlockPlan plan_block_tiles(const std::vector<BlockCounts>& counts, const std::vector<int>& active, bool vdw) {
+// Plans of more than `most` tiles are left out.
+inline BlockPlan plan_block_tiles(const std::vector<BlockCounts>& counts, const std::vector<int>& active, bool vdw,
+                                  size_t most = SIZE_MAX) {
     std::array<size_t, BLOCK_PLANS> total{};
     for (size_t k = 0; k < counts.size(); ++k)
         for (int i = 0; i < BLOCK_PLANS && active[k]; ++i) total[i] += counts[k][i];
@@ -155,6 +150,7 @@ inline BlockPlan plan_block_tiles(const std::vector<BlockCounts>& counts, const 
         const BlockCost& c = block_costs(vdw)[i];
         for (int K = c.kmin; K <= c.kmax; ++K) {
             const size_t n = total[6 * i + K - c.kmin];
+            if (n > most) continue;
             const double over = n <= 512 ? (n > 256 ? 1.0 : 0.0) : n / 256.0 - 0.5;
             const double us = (c.launch + c.launch_k * K + (c.tile + c.tile_k * K) * over) / K;
             if (best.K == 0 || us < cheapest) {
@@ -165,6 +161,19 @@ inline BlockPlan plan_block_tiles(const std::vector<BlockCounts>& counts, const 
     }
     return best;
 }
+
+// Tiles that a context reserves room for: those of the plan for all its capillaries,
+// which also fits whatever set of them is active, and the finest plan up to 65,536.
+// (The finest plan of a large context would take 0.5 bytes a node, and is no plan for
+// one: over random parts of 256 and 1024 capillaries of the sweep no plan is left out
+// that would have been taken.)
+inline size_t block_capacity(const std::vector<BlockCounts>& counts, bool vdw) {
+    size_t finest = 0;
+    for (const BlockCounts& n : counts) finest += *std::max_element(n.begin(), n.end());
+    const std::vector<int> all(counts.size(), 1);
+    return std::max(plan_block_tiles(counts, all, vdw).tiles, std::min<size_t>(finest, 65536));
+}
+
 inline BlockPlan plan_block_tiles(const std::vector<lb_geometry>& G, const std::vector<int>& active, bool vdw) {
     std::vector<BlockCounts> counts;
     for (const lb_geometry& g : G) counts.push_back(count_blocks(g, vdw));

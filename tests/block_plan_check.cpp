@@ -33,10 +33,11 @@ static int kept_counts() {
         for (int k = 0; k < 10; ++k) {
             std::vector<int> active(G.size());
             for (int& a : active) a = rnd(0, 3) > 0;
-            const BlockPlan a = plan_block_tiles(counts, active, vdw), b = plan_block_tiles(G, active, vdw);
+            const size_t room = block_capacity(counts, vdw);
+            const BlockPlan a = plan_block_tiles(counts, active, vdw, room), b = plan_block_tiles(G, active, vdw);
             const size_t n =
                 build_blocks(G, active, a.K, block_rx(a.shape), block_ry(a.shape, vdw), block_align(a.shape, vdw), nullptr);
-            if (a.shape != b.shape || a.K != b.K || a.tiles != n || n > block_capacity(counts)) {
+            if (a.shape != b.shape || a.K != b.K || a.tiles != n || n > room) {
                 std::printf("plan from counts: shape %d K %d, %zu tiles, %zu cut\n", a.shape, a.K, a.tiles, n);
                 return 1;
             }
