@@ -492,29 +492,35 @@ void launch_block_s(lb_ctx* c, const BlockArgs& a, int grid) {
         launch_block_f<BlockShape<64, 24, 12>, MODEL, CT>(c, a, grid);
 }
 
-// One launch of `steps` steps (at most block_k) of the block kernels.
+// Tiles of one kernel launch: a launch takes fewer than 2^32 threads, a tile up to 1024.
+constexpr int BLOCK_SLICE = 1 << 21;
+
+// `steps` steps (at most block_k) of the block kernels: one launch, or, for contexts of
+// more than a billion nodes, several over parts of the table (the tiles of a step do not
+// depend on each other).
 void enqueue_block(lb_ctx* c, int steps) {
-    if (c->nblocks == 0) return;
     BlockArgs a;
     a.caps = c->d_caps;
-    a.blocks = c->d_blocks;
-    a.nblocks = c->nblocks;
     a.arena0 = c->arena[0];
     a.arena1 = c->arena[1];
     a.cur = c->cur;
     a.halo = 2 * c->block_k;
     a.steps = steps;
-    const int grid = 8 * ((c->nblocks + 7) / 8);
-    if (c->model == LB_VDW) {
-        if (c->cfg.fp64_arith)
-            launch_block_s<0, double>(c, a, grid);
-        else
-            launch_block_s<0, float>(c, a, grid);
-    } else {
-        if (c->cfg.fp64_arith)
-            launch_block_s<1, double>(c, a, grid);
-        else
-            launch_block_s<1, float>(c, a, grid);
+    for (int first = 0; first < c->nblocks; first += BLOCK_SLICE) {
+        a.blocks = c->d_blocks + first;
+        a.nblocks = std::min(BLOCK_SLICE, c->nblocks - first);
+        const int grid = 8 * ((a.nblocks + 7) / 8);
+        if (c->model == LB_VDW) {
+            if (c->cfg.fp64_arith)
+                launch_block_s<0, double>(c, a, grid);
+            else
+                launch_block_s<0, float>(c, a, grid);
+        } else {
+            if (c->cfg.fp64_arith)
+                launch_block_s<1, double>(c, a, grid);
+            else
+                launch_block_s<1, float>(c, a, grid);
+        }
     }
 }
 

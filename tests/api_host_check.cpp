@@ -342,6 +342,31 @@ static int captured_calls_can_be_replayed() {
     return 0;
 }
 
+// The tiles of a context of billions of nodes go to launches of fewer than 2^32 threads,
+// each tile once.
+static int large_tables_in_several_launches() {
+    for (lb_model m : {LB_VDW, LB_BINARY})
+        for (int shape = 0; shape < BLOCK_SHAPES; ++shape) {
+            lb_ctx* c = context(m, {SMALL});
+            EXPECT(c);
+            c->block_shape = shape;
+            for (int n : {1, BLOCK_SLICE, BLOCK_SLICE + 1, 6000000}) {
+                c->nblocks = n;   // (the kernels do not run)
+                rt.launches.clear();
+                enqueue_block(c, c->block_k);
+                EXPECT(hipGetLastError() == hipSuccess);
+                const BlockDev* at = c->d_blocks;
+                for (const Launched& l : rt.launches) {
+                    EXPECT(l.block.blocks == at && l.block.steps == c->block_k);
+                    at += l.block.nblocks;
+                }
+                EXPECT(at == c->d_blocks + n);
+            }
+            lb_free(c);
+        }
+    return 0;
+}
+
 int main(int argc, char** argv) {
     const struct {
         const char* name;
@@ -354,6 +379,7 @@ int main(int argc, char** argv) {
         {"tuner_times_whole_launches", tuner_times_whole_launches},
         {"read_outs_are_coherent", read_outs_are_coherent},
         {"captured_calls_can_be_replayed", captured_calls_can_be_replayed},
+        {"large_tables_in_several_launches", large_tables_in_several_launches},
         {"tiles_with_fluid", tiles_with_fluid},
         {"no_device_memory_beside_the_state", no_device_memory_beside_the_state},
     };

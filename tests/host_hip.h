@@ -32,6 +32,7 @@ struct HostRuntime {
     bool pending = false;         // work was enqueued and not waited for
     int destroyed_pending = 0;    // executable graphs destroyed meanwhile
     bool capturing = false;
+    hipError_t last_error = hipSuccess;
     int count(const char* part) const {
         int n = 0;
         for (const Launched& l : launches) n += l.kernel.find(part) != std::string::npos;
@@ -58,14 +59,22 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* shm, hipStream_t*
     *g = g_cfg.g, *b = g_cfg.b, *shm = g_cfg.shm, *s = g_cfg.s;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t) {
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t, hipStream_t) {
+    if (block.x * block.y > 1024 || grid.x * (uint64_t)block.x > 0xffffffffu) {
+        rt.last_error = hipErrorInvalidConfiguration;
+        return rt.last_error;
+    }
     Launched l{rt.names[f], rt.capturing, {}};
     if (l.kernel.find("lb_block") != std::string::npos) l.block = *(const lbk::BlockArgs*)args[0];
     rt.launches.push_back(l);
     rt.pending = rt.pending || !rt.capturing;
     return hipSuccess;
 }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetLastError() {
+    const hipError_t e = rt.last_error;
+    rt.last_error = hipSuccess;
+    return e;
+}
 const char* hipGetErrorString(hipError_t) { return "host runtime error"; }
 hipError_t hipGetDeviceCount(int* n) {
     *n = 1;
